@@ -84,8 +84,9 @@ constexpr size_t kScratchBytes = (2 * tsq::kReduceBlocks + 2) * sizeof(double);
 // Default schedule.  Steps per pass: 5 with the register phase ring (within a
 // few percent of the fastest schedule for both dtypes at 4096^2).  Segment
 // height: as many wavefront tiles as the device holds resident at once (one
-// round, no tail of a partly filled second round), each segment at least 2K
-// row pairs long so the discarded warm-up pairs stay below half the work.
+// round, no tail of a partly filled second round) while segments of at least
+// 2K row pairs keep the discarded warm-up pairs below half the work; smaller
+// meshes: see default_seg_rows.
 constexpr int kDefaultSteps = 5;
 
 // Fill the zero fields of a requested schedule with defaults; false if the
@@ -152,8 +153,28 @@ int default_seg_rows(const tsq_plan* p, int steps, bool last, int ppl, bool lds,
     if (segs < 1) segs = 1;
     if (segs > pairs) segs = pairs;
     long long pairs_per_seg = (pairs + segs - 1) / segs;
-    const long long min_pairs = 2LL * (steps + (last ? 1 : 0));
-    if (pairs_per_seg < min_pairs) pairs_per_seg = min_pairs;
+    const long long K = steps + (last ? 1 : 0);
+    if (pairs_per_seg >= 2 * K) return (int)(2 * pairs_per_seg);
+    // A mesh too small for segments of 2K pairs in one round: a pass lasts as
+    // long as its busiest SIMD, which marches its wavefronts' Q + K pairs (the
+    // pipeline's fill skipped) one behind the other, each pair 0.22 us a step
+    // alone (complex64, 1 wavefront per SIMD) and about 0.85 of that per
+    // wavefront when two or more share the SIMD.  The height with the least of
+    // that, a block of kWavesPerBlock wavefronts per compute unit: 1030 x 614
+    // complex64 at 5 steps per pass takes 8 rows, 13.9 us a pass against 20.8 at
+    // 2K pairs (6 rows, two blocks on some units: 17.3); 256^2 takes 2 rows,
+    // 10.1 against 18.9 us.
+    const long long groups = strip_slots / tsq::kWavesPerBlock;
+    double best = 0.0;
+    for (long long q = 1; q <= 2 * K; ++q) {
+        const long long blocks = groups * ((pairs + q - 1) / q);
+        const long long per_cu = (blocks + cus - 1) / cus;
+        const double cost = (double)(q + K) * std::max(1.0, 0.85 * (double)per_cu);
+        if (q == 1 || cost < best) {
+            best = cost;
+            pairs_per_seg = q;
+        }
+    }
     return (int)(2 * pairs_per_seg);
 }
 
