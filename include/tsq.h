@@ -141,6 +141,11 @@ typedef struct {
                                 (pairs_per_lane 1), 0 = default (registers up to 6
                                 steps per pass, else LDS) */
 } tsq_schedule;
+/* With every field 0 (also a new plan's schedule) the library may run a small
+ * 2D mesh, up to about 1000^2 sites, in tile kernels instead of the march:
+ * every row pair of a block works on a step at once, 1..14 steps per pass
+ * dealt evenly over the passes, the same bits.  tsq_evolve_passes counts them;
+ * tsq_plan_get_schedule still returns the march's defaults. */
 
 /* Set the plan's schedule (host only).  Zero fields take their defaults;
  * tsq_plan_get_schedule returns the resolved values (segment_rows stays 0 when

@@ -1,0 +1,10 @@
+// Tile kernel instances (small 2D meshes): complex64.
+#include "tsq_tile.hpp"
+
+namespace tsq {
+
+const void* tile_ptr_c64(int pairs_per_wave, bool closed, bool td, bool u4) {
+    return pick_tile<C64>(pairs_per_wave, closed, td, u4);
+}
+
+}  // namespace tsq

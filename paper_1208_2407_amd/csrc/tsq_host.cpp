@@ -29,6 +29,12 @@ struct SubStep {
     size_t off_ptab;
 };
 
+// Passes of an evolution of a small mesh by the tile kernels (tsq_tile.hpp).
+struct TilePasses {
+    int rp = 0;          // row pairs per wavefront; 0: the march runs the evolution
+    int64_t passes = 0;  // the steps are dealt evenly over them
+};
+
 struct tsq_plan {
     tsq_problem p;
     double Jx, Jy, Jz, eps0;
@@ -38,6 +44,10 @@ struct tsq_plan {
     int nkinds;
     SubStep kind[2];
     tsq_schedule sched;   // resolved (segment_rows may stay 0 = per launch)
+    bool sched_default;   // every field was left to the library (small meshes: tile kernels)
+    mutable int64_t tile_steps;     // pick_tile's last answer: for these steps (-1: none) ...
+    mutable bool tile_td;
+    mutable TilePasses tile_passes;
     size_t sites, elem, pelem;
     size_t off_psi2, off_ptab, off_scratch, off_turns, ws_bytes;
     const void* ws_bound;
@@ -283,6 +293,71 @@ bool pass_groups(const tsq_plan* p, int64_t steps, int S, std::vector<PassGroup>
         return false;
     }
     return true;
+}
+
+// Steps of pass i: the steps + 1 stages (the closing odd factors are one) dealt
+// evenly, so no pass runs more than ceil((steps + 1) / passes) stages.
+int64_t tile_steps_before(const TilePasses& t, int64_t steps, int64_t i) {
+    return i == t.passes ? steps : (int64_t)((__int128)(steps + 1) * i / t.passes);
+}
+
+// Whether the tile kernels run this evolution, and in how many passes: the
+// plan's schedule is the library's choice and they are expected faster than
+// the march.  Expected times of a pass in us, from timed passes on an MI355X
+// (complex64 | complex128): tile, 16 row pairs 3.6 + 0.58 K | 4.2 + 0.6 K, 32 row
+// pairs 4.3 + 1.0 K | 6.2 + 0.95 K while every compute unit has one block, per
+// block of a unit beyond that; plus reading the mesh at the start with nothing
+// to overlap it (0.1 us per MB); the march 0.22 us per stage run of its busiest
+// SIMD (see default_seg_rows).  Both sides at 200+ steps, us per step, march
+// against tile: 64^2 1.98 : 1.17, 512^2 2.25 : 1.34, 1030 x 614 2.72 : 1.65
+// (complex128 2.75 : 2.14), 1500^2 4.6 : 4.3; beyond two blocks per unit the
+// march is the faster.
+TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
+    TilePasses best;
+    if (!p->sched_default || p->three_d || steps < 1) return best;
+    const bool u4 = fused_order4(p);
+    if (p->p.order == 4 && !u4) return best;  // closed fourth order runs kind by kind
+    int cus = device_cus();
+    if (cus <= 0) cus = 256;
+    // the tallest tiles at the fewest stages: no more blocks per unit than two, or never
+    if (tsq::tile_geometry(p->p.nx, p->p.ny, 2, false, 2).tiles > 2LL * cus) return best;
+    if (p->tile_steps == steps && p->tile_td == td) return p->tile_passes;
+    const double launch = 2.2;
+    const bool closed = p->p.bc == TSQ_BC_CLOSED;
+    const double mb = 1e-6 * 3.0 * (double)(p->sites * p->elem);
+    // the march, steady passes
+    const int S0 = u4 ? 5 : td ? std::min(p->sched.steps_per_pass, tsq::kMaxTdSteps)
+                               : p->sched.steps_per_pass;
+    const bool lds0 = u4 || p->sched.phase_store == 2;
+    const int rows0 = default_seg_rows(p, S0, false, 1, lds0, closed, td, u4);
+    const tsq::MarchGeometry g0 = tsq::march_geometry(p->p.nx, p->p.ny, S0, false, 1, rows0);
+    const int64_t n0 = (g0.blocks + cus - 1) / cus;
+    const double march = launch + 0.22 * S0 * (rows0 / 2 + S0) * std::max(1.0, 0.85 * (double)n0);
+    double cost = march * (u4 ? (double)steps : std::ceil((double)steps / S0));
+    for (int rp = 1; rp <= (u4 ? 1 : 2); ++rp) {
+        const int most = tsq::kTileWaves * rp / 2 - 1;  // stages that leave a pair to store
+        for (int K = 2; K <= most; ++K) {
+            if (u4 ? K != 6 : (td && K > tsq::kMaxSteps)) continue;
+            const int Kr = u4 ? 5 : K;  // stages of a steady pass
+            const tsq::MarchGeometry g = tsq::tile_geometry(p->p.nx, p->p.ny, Kr, false, rp);
+            const int64_t n = (g.tiles + cus - 1) / cus;
+            if (n > 2) continue;
+            const double t = launch + 0.1 * mb + (double)n * (rp == 1 ? 1.3 + 0.6 * Kr : 2.0 + 1.0 * Kr);
+            int64_t passes = u4 ? steps : (steps + 1 + K - 1) / K;
+            if (!u4 && (passes & 1) && steps > 1) ++passes;  // an odd count ends with a copy
+            if (!u4 && steps == 1) passes = 1;
+            const double c = t * (double)passes;
+            if (c < cost) {
+                cost = c;
+                best.rp = rp;
+                best.passes = passes;
+            }
+        }
+    }
+    p->tile_steps = steps;
+    p->tile_td = td;
+    p->tile_passes = best;
+    return best;
 }
 
 int64_t run_passes(const std::vector<Run>& runs) {
@@ -728,6 +803,8 @@ int tsq_plan_create(const tsq_problem* pr, tsq_plan** out) {
     p->ox2 = p->kind[0].ox2;
     p->oy2 = p->kind[0].oy2;
     resolve_schedule(tsq_schedule{0, 0, 0, 0}, p->sched);
+    p->sched_default = true;
+    p->tile_steps = -1;
     p->sites = (size_t)pr->nx * (size_t)pr->ny * (size_t)p->p.nz;
     p->elem = pr->dtype == TSQ_C128 ? 16 : 8;
     // bytes per site of a phase-table area: complex128 exp(-i phi) (16);
@@ -784,6 +861,9 @@ int tsq_plan_set_schedule(tsq_plan* plan, const tsq_schedule* sc) {
     if (plan->p.bc == TSQ_BC_CLOSED && r.pairs_per_lane != 1)
         return fail(TSQ_ERR_ARG, "closed meshes run with 1 pair per lane");
     plan->sched = r;
+    plan->tile_steps = -1;
+    plan->sched_default = !sc->steps_per_pass && !sc->segment_rows && !sc->pairs_per_lane &&
+                          !sc->phase_store;
     return ok();
 }
 
@@ -807,6 +887,12 @@ int tsq_evolve_passes(const tsq_plan* plan, int64_t steps, int64_t* passes, int3
     if (fused_order4(plan)) {  // one pass per fourth-order step
         *passes = steps;
         *copy_back = (steps & 1) ? 1 : 0;
+        return ok();
+    }
+    const TilePasses tile = pick_tile(plan, steps, plan->td);
+    if (tile.rp) {
+        *passes = tile.passes;
+        *copy_back = (int32_t)(tile.passes & 1);
         return ok();
     }
     std::vector<PassGroup> groups;
@@ -906,6 +992,13 @@ int check_evolve(const tsq_plan* plan, const void* psi, int64_t steps, const voi
     return TSQ_OK;
 }
 
+// An evolution that ended in the second buffer: copy the state back to psi.
+int copy_result(const tsq_plan* plan, void* psi, const void* from, hipStream_t s) {
+    hipError_t e = hipMemcpyAsync(psi, from, plan->sites * plan->elem, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "copy back: %s", hipGetErrorString(e));
+    return ok();
+}
+
 // Fourth order on a periodic 2D mesh: one pass per step, sub-steps p, p, m,
 // p, p with both phase tables; an odd pass count ends with a copy back.
 int run_evolution_order4(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) {
@@ -930,6 +1023,7 @@ int run_evolution_order4(tsq_plan* plan, void* psi, int64_t steps, void* ws, hip
     d.myh = m.oyh;
     d.log_table_p = table_log(plan, 0);
     d.log_table_m = table_log(plan, 1);
+    const TilePasses tile = pick_tile(plan, steps, false);
     for (int64_t i = 0; i < steps; ++i) {
         d.src = buf[i & 1];
         d.dst = buf[(i + 1) & 1];
@@ -938,14 +1032,11 @@ int run_evolution_order4(tsq_plan* plan, void* psi, int64_t steps, void* ws, hip
         d.seg_rows = plan->sched.segment_rows
                          ? plan->sched.segment_rows
                          : default_seg_rows(plan, 5, d.last, 1, true, false, false, true);
-        hipError_t e = tsq::launch_pass(plan->p.dtype, d, s);
+        hipError_t e = tile.rp ? tsq::launch_tile(plan->p.dtype, d, tile.rp, s)
+                               : tsq::launch_pass(plan->p.dtype, d, s);
         if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "order-4 pass launch: %s", hipGetErrorString(e));
     }
-    if (steps & 1) {
-        hipError_t e = hipMemcpyAsync(psi, buf[1], plan->sites * plan->elem, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "copy back: %s", hipGetErrorString(e));
-    }
-    return ok();
+    return steps & 1 ? copy_result(plan, psi, buf[1], s) : ok();
 }
 
 // Launch the passes of `steps` steps (f: per-step modulation of a
@@ -960,8 +1051,6 @@ int run_evolution(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_
                      : plan->sched.steps_per_pass;
     const int ppl = plan->sched.pairs_per_lane;
     const bool lds = plan->sched.phase_store == 2;
-    std::vector<PassGroup> groups;
-    const bool copy_back = pass_groups(plan, steps, S, groups);
 
     tsq::PassDesc d;
     d.nx = plan->p.nx;
@@ -971,6 +1060,30 @@ int run_evolution(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_
     d.closed = plan->p.bc == TSQ_BC_CLOSED;
     d.td = td;
     d.ptab2 = td ? w + plan->off_turns : nullptr;
+    const TilePasses tile = pick_tile(plan, steps, td);
+    if (tile.rp) {
+        const SubStep& u = plan->kind[0];
+        d.ptab = w + u.off_ptab;
+        d.oxh = u.oxh;
+        d.oyh = u.oyh;
+        d.ox2 = u.ox2;
+        d.oy2 = u.oy2;
+        for (int64_t k = 0; k < tile.passes; ++k) {
+            const int64_t n0 = tile_steps_before(tile, steps, k);
+            d.src = buf[k & 1];
+            d.dst = buf[(k + 1) & 1];
+            d.steps = (int)(tile_steps_before(tile, steps, k + 1) - n0);
+            d.first = k == 0;
+            d.last = k + 1 == tile.passes;
+            d.f = td ? f + n0 : nullptr;
+            hipError_t e = tsq::launch_tile(plan->p.dtype, d, tile.rp, s);
+            if (e != hipSuccess)
+                return fail(TSQ_ERR_DEVICE, "step pass launch: %s", hipGetErrorString(e));
+        }
+        return tile.passes & 1 ? copy_result(plan, psi, buf[1], s) : ok();
+    }
+    std::vector<PassGroup> groups;
+    const bool copy_back = pass_groups(plan, steps, S, groups);
     int64_t i = 0, n0 = 0;  // pass index, first step of the pass
     for (const PassGroup& g : groups) {
         const SubStep& u = plan->kind[g.kind];
@@ -995,11 +1108,7 @@ int run_evolution(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_
             n0 += g.size;
         }
     }
-    if (copy_back) {
-        hipError_t e = hipMemcpyAsync(psi, buf[1], plan->sites * plan->elem, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "copy back: %s", hipGetErrorString(e));
-    }
-    return ok();
+    return copy_back ? copy_result(plan, psi, buf[1], s) : ok();
 }
 
 // Three-dimensional mesh: one step per pass.
@@ -1041,11 +1150,8 @@ int run_evolution3(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream
         hipError_t e = tsq::launch_pass3(plan->p.dtype, d, s);
         if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "3D pass launch: %s", hipGetErrorString(e));
     }
-    if (!(steps & 1)) {  // steps + 1 passes: an odd count ends in the second buffer
-        hipError_t e = hipMemcpyAsync(psi, buf[1], plan->sites * plan->elem, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "copy back: %s", hipGetErrorString(e));
-    }
-    return ok();
+    // steps + 1 passes: an odd count ends in the second buffer
+    return steps & 1 ? ok() : copy_result(plan, psi, buf[1], s);
 }
 
 }  // namespace

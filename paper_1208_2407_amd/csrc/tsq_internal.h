@@ -51,6 +51,7 @@ constexpr int kMaxTdSteps = 6;   // deepest fusion with a time-dependent potenti
 constexpr int kTurns = 2048;     // time-dependent phase: factors exp(-i j pi/1024), j mod 2048
 constexpr int kWaveSize = 64;
 constexpr int kWavesPerBlock = 4;
+constexpr int kTileWaves = 16;   // wavefronts of a tile kernel's block (small meshes)
 
 // Geometry the march kernel uses (shared by host-side launch arithmetic).
 struct MarchGeometry {
@@ -62,6 +63,9 @@ struct MarchGeometry {
 };
 MarchGeometry march_geometry(int nx, int ny, int steps, bool last, int pairs_per_lane,
                              int seg_rows);
+// Geometry of a tile kernel's pass with `rp` row pairs per wavefront:
+// segments of 2 (kTileWaves rp - 2K) rows, one block per strip and segment.
+MarchGeometry tile_geometry(int nx, int ny, int steps, bool last, int rp);
 
 // Kernel arguments of one pass over one problem (also the job record of the
 // batched kernel, uploaded to device memory).  R = double (complex128) or
@@ -122,6 +126,7 @@ struct MarchArgs {
     R c1xs, c1xd, c1ys, c1yd;  // odd factors closing the evolution, tau = dt/2
     double g[kMaxSteps];       // time-dependent potential: f_n of step k of the pass
     double kxw, kyw;           // closed, time-dependent: scale of the last odd column, row
+    int tile_steps, tile_last; // tile kernel: steps of the pass, closing odd factors after them
     Order4Coefs<R> u4;         // fourth order in one pass per step
 };
 
@@ -169,6 +174,8 @@ MarchArgs<R> make_march_args(const PassDesc& d, const MarchGeometry& g) {
     a.seg_rows = d.seg_rows;
     a.nstrips = g.nstrips;
     a.nsegs = g.nsegs;
+    a.tile_steps = d.steps;
+    a.tile_last = d.last ? 1 : 0;
     const Coef64& ox1 = d.first ? d.oxh : d.ox2;
     const Coef64& oy1 = d.first ? d.oyh : d.oy2;
     if (d.closed) {
@@ -273,6 +280,10 @@ hipError_t launch_td_table(const double* V0, const double* W, void* table, void*
                            long long sites, double dt, double eps0, double hbar, double scale,
                            hipStream_t s);
 hipError_t launch_pass(int dtype, const PassDesc& d, hipStream_t s);
+// The same pass by the tile kernel with `rp` (1 or 2) row pairs per wavefront;
+// d.steps + d.last < kTileWaves rp / 2 (time-dependent: d.steps <= kMaxSteps),
+// fourth order rp = 1 only.  d.seg_rows, pairs_per_lane and phase_lds are not used.
+hipError_t launch_tile(int dtype, const PassDesc& d, int rp, hipStream_t s);
 // Second stage of the FP64 reductions: sum the `nblocks` (norm, energy) partials
 // in a fixed order into result[0] = norm, result[1] = energy / norm.
 hipError_t launch_observables_final(const double* partial, int nblocks, double* result,

@@ -23,6 +23,9 @@ const void* march_ptr_c128_closedtd(int steps, bool last, int ppl, bool lds);
 const void* march_ptr_c64_closedtd(int steps, bool last, int ppl, bool lds);
 const void* march_ptr_c128_order4(int steps, bool last, int ppl, bool lds);
 const void* march_ptr_c64_order4(int steps, bool last, int ppl, bool lds);
+// Tile kernels (tile_<dtype>.hip)
+const void* tile_ptr_c128(int pairs_per_wave, bool closed, bool td, bool u4);
+const void* tile_ptr_c64(int pairs_per_wave, bool closed, bool td, bool u4);
 
 namespace {
 
@@ -66,7 +69,44 @@ hipError_t launch_with(const void* f, const PassDesc& d, hipStream_t s) {
     return hipLaunchKernel(f, dim3(g.blocks), dim3(kWaveSize * kWavesPerBlock), params, 0, s);
 }
 
+template <class R>
+hipError_t launch_tile_with(const void* f, const PassDesc& pass, int rp, hipStream_t s) {
+    PassDesc d = pass;
+    const MarchGeometry g = tile_geometry(d.nx, d.ny, d.steps, d.last, rp);
+    d.seg_rows = 2 * (kTileWaves * rp - 2 * (d.steps + (d.last ? 1 : 0)));
+    MarchArgs<R> a = make_march_args<R>(d, g);
+    void* params[] = {&a};
+    return hipLaunchKernel(f, dim3(g.blocks), dim3(kWaveSize * kTileWaves), params, 0, s);
+}
+
 }  // namespace
+
+MarchGeometry tile_geometry(int nx, int ny, int steps, bool last, int rp) {
+    MarchGeometry g;
+    const int K = steps + (last ? 1 : 0);
+    const int pairs = (ny + 1) / 2, out = kTileWaves * rp - 2 * K;
+    g.halo_lanes = K;
+    g.strip_sites = (kWaveSize - 2 * K) * 2;
+    g.nstrips = (nx + g.strip_sites - 1) / g.strip_sites;
+    g.nsegs = (pairs + out - 1) / out;
+    g.tiles = (long long)g.nstrips * g.nsegs;
+    g.blocks = (int)g.tiles;
+    return g;
+}
+
+hipError_t launch_tile(int dtype, const PassDesc& d, int rp, hipStream_t s) {
+    const int K = d.steps + (d.last ? 1 : 0);
+    if (rp < 1 || rp > 2 || d.steps < 1 || 2 * K >= kTileWaves * rp || (d.td && d.steps > kMaxSteps) ||
+        (d.u4 && (rp != 1 || d.steps != 5)))
+        return hipErrorInvalidValue;
+    const void* f = dtype == 1 ? tile_ptr_c128(rp, d.closed, d.td, d.u4)
+                               : tile_ptr_c64(rp, d.closed, d.td, d.u4);
+    if (!f) return hipErrorInvalidValue;
+    hipError_t e = dtype == 1 ? launch_tile_with<double>(f, d, rp, s)
+                              : launch_tile_with<float>(f, d, rp, s);
+    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
 
 MarchGeometry march_geometry(int nx, int ny, int steps, bool last, int pairs_per_lane,
                              int seg_rows) {
