@@ -125,9 +125,9 @@ int tsq_plan_destroy(tsq_plan* plan);
  * p dt and (1-4p) dt) and reduction scratch.  Host only. */
 int tsq_workspace_size(const tsq_plan* plan, size_t* bytes);
 
-/* Schedule of the fused step kernel (2D meshes; a 3D mesh runs one step per
- * pass with its own tiling and takes only segment_rows, as the planes one
- * block marches).  Every schedule applies the same
+/* Schedule of the fused step kernel (2D meshes; a 3D mesh runs one or two steps
+ * per pass, by its size, with its own tiling and takes only segment_rows, as
+ * the planes one block marches).  Every schedule applies the same
  * operations in the same order to every site, so results are bitwise
  * identical across schedules; only speed changes. */
 typedef struct {
@@ -161,7 +161,9 @@ int tsq_plan_get_schedule(const tsq_plan* plan, tsq_schedule* schedule);
  * under the plan's schedule, and whether it ends with a device-to-device copy
  * (odd pass count that cannot be split).  Order-4 plans of periodic 2D meshes
  * run one pass per fourth-order step (its five second-order sub-steps fused,
- * whatever steps_per_pass says).  Host only.  Errors: TSQ_ERR_ARG. */
+ * whatever steps_per_pass says).  A 3D mesh is counted as one pass per step and
+ * a closing one, steps + 1, whether or not its passes fuse two steps.  Host
+ * only.  Errors: TSQ_ERR_ARG. */
 int tsq_evolve_passes(const tsq_plan* plan, int64_t steps, int64_t* passes, int32_t* copy_back);
 
 /* The diagonal part H0 of Sec. 2 (potential plus the mesh's on-site term
@@ -181,8 +183,9 @@ int tsq_set_potential(tsq_plan* plan, const double* V_dev, void* ws, size_t ws_b
  * (order 4: U4(dt) of Eq. "fourthorder") to psi_dev in place (device,
  * contiguous, 16-byte aligned): several steps are fused per read and write of
  * psi (the schedule's steps_per_pass), consecutive odd factors merged.  On
- * periodic 2D meshes the even and odd-y factors rotate in the tangent form
- * (a, b) <- (a + i t b, b + i t a), t = tan al, and the phase factor and the
+ * periodic 2D meshes, and on 3D meshes whose angles |dt| hbar / (2 m da^2) stay
+ * below 1 rad per step, the even and odd-y (and z) factors rotate in the tangent
+ * form (a, b) <- (a + i t b, b + i t a), t = tan al, and the phase factor and the
  * odd-x factors opening and closing the evolution restore the product of the
  * cosines; on closed 2D meshes the even factors rotate in the tangent form and
  * the phase factor restores their cosines site by site.  Equal to the block

@@ -40,6 +40,7 @@ struct tsq_plan {
     double Jx, Jy, Jz, eps0;
     bool three_d;                    // nz >= 2
     tsq::Coef64 ozh, oz2;            // z factors of a 3D mesh, tau = dt/2 and dt
+    bool slab3;                      // 3D: the slab march (tangent form)
     tsq::Coef64 oxh, oyh, ox2, oy2;   // of kind 0
     int nkinds;
     SubStep kind[2];
@@ -198,6 +199,11 @@ bool fused_order4(const tsq_plan* p) {
 // 2D meshes the cosines of a steady step of that kind (the tangent-form factors
 // leave them out), from the tangents rounded in the plan's dtype; else 0.
 double table_log(const tsq_plan* p, int k) {
+    if (p->three_d && p->slab3) {
+        const tsq::Coef64 oh[3] = {p->oxh, p->oyh, p->ozh}, o2[3] = {p->ox2, p->oy2, p->oz2};
+        return p->p.dtype == TSQ_C128 ? tsq::step3_log_sec2<double>(oh, o2)
+                                      : tsq::step3_log_sec2<float>(oh, o2);
+    }
     if (p->three_d || p->p.bc != TSQ_BC_PERIODIC) return 0.0;
     const SubStep& u = p->kind[k];
     return p->p.dtype == TSQ_C128 ? tsq::step_log_sec2<double>(u.oxh, u.oyh, u.ox2, u.oy2)
@@ -802,6 +808,11 @@ int tsq_plan_create(const tsq_problem* pr, tsq_plan** out) {
     p->oyh = p->kind[0].oyh;
     p->ox2 = p->kind[0].ox2;
     p->oy2 = p->kind[0].oy2;
+    // 3D meshes: the slab march rotates in the tangent form too; larger steps (and
+    // planes beyond its 32-bit offsets) run one step per pass in the delta form
+    p->slab3 = three_d && std::fabs(p->ox2.al) < kMaxAngle && std::fabs(p->oy2.al) < kMaxAngle &&
+              std::fabs(p->oz2.al) < kMaxAngle &&
+              (long long)pr->nx * pr->ny * (pr->dtype == TSQ_C128 ? 16 : 8) <= tsq::kMaxSlabPlane;
     resolve_schedule(tsq_schedule{0, 0, 0, 0}, p->sched);
     p->sched_default = true;
     p->tile_steps = -1;
@@ -879,7 +890,7 @@ int tsq_evolve_passes(const tsq_plan* plan, int64_t steps, int64_t* passes, int3
     if (plan->p.order == 4 && steps > 10000000LL)
         return fail(TSQ_ERR_ARG, "order-4 evolution of %lld steps is too long for one call",
                     (long long)steps);
-    if (plan->three_d) {  // one step per pass, then a closing pass
+    if (plan->three_d) {  // counted as one step per pass, then a closing pass
         *passes = steps > 0 ? steps + 1 : 0;
         *copy_back = (steps > 0 && !(steps & 1)) ? 1 : 0;
         return ok();
@@ -1111,7 +1122,98 @@ int run_evolution(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_
     return copy_back ? copy_result(plan, psi, buf[1], s) : ok();
 }
 
-// Three-dimensional mesh: one step per pass.
+// One kind of pass of the slab march over a mesh: stages, row pairs per
+// wavefront, plane pairs per tile.
+struct SlabPass {
+    int stages, rp, seg_pairs;
+};
+
+// Plane pairs per tile: the blocks go in rounds of one per compute unit, each
+// marching a tile's Q pairs and its halo (a pair per stage and side, half of them
+// without the second stage), and every tile reads its halo: the segment count
+// with the least sum of the two, in pairs per unit.  At 512^3 complex64 two
+// segments (220 tiles on 256 units).
+SlabPass slab_pass(const tsq_plan* p, int stages, int rp, long long cus) {
+    SlabPass r{stages, rp, 1};
+    const int strip = tsq::slab_strip(stages), slab = tsq::slab_pairs(stages, rp);
+    const long long columns = (long long)((p->p.nx + strip - 1) / strip) * ((p->p.ny / 2 + slab - 1) / slab);
+    const long long pairs = p->p.nz / 2;
+    double best = 0.0;
+    for (long long segs = 1; segs <= pairs; ++segs) {
+        const long long q = (pairs + segs - 1) / segs;
+        const long long tiles = columns * ((pairs + q - 1) / q);
+        const long long rounds = (tiles + cus - 1) / cus;
+        const double cost = (double)rounds * (double)(q + 2 * stages - 1) +
+                            (double)(tiles * (q + 2 * stages)) / (double)cus;
+        if (segs == 1 || cost < best) {
+            best = cost;
+            r.seg_pairs = (int)q;
+        }
+        if (q <= 1) break;
+    }
+    if (p->sched.segment_rows > 0)
+        r.seg_pairs = (int)std::min<long long>(pairs, p->sched.segment_rows / 2);
+    return r;
+}
+
+// Three-dimensional mesh by the slab march: passes of two steps (small meshes:
+// one), then the closing odd factors: with a last single step in one pass, or by
+// themselves from whichever buffer holds the state to psi.
+int run_slab(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) {
+    char* w = static_cast<char*>(ws);
+    void* buf[2] = {psi, w + plan->off_psi2};
+    int cus = device_cus();
+    if (cus <= 0) cus = 256;
+    tsq::Pass3Desc d;
+    d.ptab = w + plan->kind[0].off_ptab;
+    d.nx = plan->p.nx;
+    d.ny = plan->p.ny;
+    d.nz = plan->p.nz;
+    d.oh[0] = plan->oxh;
+    d.oh[1] = plan->oyh;
+    d.oh[2] = plan->ozh;
+    d.o2[0] = plan->ox2;
+    d.o2[1] = plan->oy2;
+    d.o2[2] = plan->oz2;
+    // One stage below 1.5M sites, where a pass lasts as long as a block's few
+    // iterations; two stages above, where it is bound by memory; complex64 with
+    // two row pairs per wavefront (a smaller y halo, half the blocks) from 6M.
+    // Steady us per step, complex64 one stage | two, 1 pair | two, 2 pairs:
+    // 96^3 7.9 | 8.4 | 11.7, 128 x 160 x 192 24.8 | 21.3 | 23.3, 192^3 37.9 | 35.4 |
+    // 31.8, 512^3 769 | 557 | 472; complex128 one | two: 96^3 13.0 | 13.7, 128^3 34.0
+    // | 30.4, 512^3 1515 | 1138.
+    const bool two_steps = plan->sites >= 1500000;
+    const int rp = plan->p.dtype == TSQ_C64 && plan->sites >= 6000000 ? 2 : 1;
+    const SlabPass one = slab_pass(plan, 1, 1, cus), two = slab_pass(plan, 2, rp, cus);
+    const int64_t pairs2 = two_steps ? steps / 2 : 0;  // two-step passes
+    int64_t ones = steps - 2 * pairs2;               // single-step passes before the closing
+    // an odd count's last step takes the closing factors along where that leaves
+    // the state in psi
+    const bool along = two_steps && ones == 1 && ((pairs2 + 1) & 1) == 0;
+    if (along) ones = 0;
+    const int64_t passes = pairs2 + ones + (along ? 1 : 0);
+    for (int64_t i = 0; i < passes; ++i) {
+        const SlabPass& k = i < pairs2 || along ? two : one;
+        d.src = buf[i & 1];
+        d.dst = buf[(i + 1) & 1];
+        d.first = i == 0;
+        d.close = along && i + 1 == passes;
+        d.stages = k.stages;
+        d.rp = k.rp;
+        d.seg_pairs = k.seg_pairs;
+        hipError_t e = tsq::launch_slab(plan->p.dtype, d, s);
+        if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "3D pass launch: %s", hipGetErrorString(e));
+    }
+    if (along) return ok();
+    d.src = buf[passes & 1];
+    d.dst = psi;
+    hipError_t e = tsq::launch_close3(plan->p.dtype, d, s);
+    if (e != hipSuccess) return fail(TSQ_ERR_DEVICE, "3D closing pass launch: %s", hipGetErrorString(e));
+    return ok();
+}
+
+// Three-dimensional mesh whose angles are beyond the tangent form (or whose planes
+// are beyond the slab march's offsets): one step per pass in the delta form.
 int run_evolution3(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) {
     char* w = static_cast<char*>(ws);
     void* buf[2] = {psi, w + plan->off_psi2};
@@ -1164,6 +1266,8 @@ int tsq_evolve(tsq_plan* plan, void* psi, int64_t steps, void* ws, size_t ws_byt
     if (plan->td)
         return fail(TSQ_ERR_STATE, "the workspace holds a time-dependent potential: use tsq_evolve_td");
     if (steps == 0) return ok();
+    if (plan->three_d && plan->slab3)
+        return run_slab(plan, psi, steps, ws, static_cast<hipStream_t>(stream));
     if (plan->three_d) return run_evolution3(plan, psi, steps, ws, static_cast<hipStream_t>(stream));
     return run_evolution(plan, psi, steps, ws, static_cast<hipStream_t>(stream), nullptr);
 }

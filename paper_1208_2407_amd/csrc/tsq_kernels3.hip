@@ -9,6 +9,10 @@ namespace tsq {
 
 const void* march3_ptr_c128(bool close);
 const void* march3_ptr_c64(bool close);
+const void* slab_ptr_c128(int stages, int rp, bool close);
+const void* slab_ptr_c64(int stages, int rp, bool close);
+const void* close3_ptr_c128();
+const void* close3_ptr_c64();
 
 namespace {
 
@@ -117,6 +121,68 @@ static hipError_t launch3_with(const void* f, const Pass3Desc& d, hipStream_t s)
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     void* params[] = {&a};
     return hipLaunchKernel(f, dim3((unsigned)tiles), dim3(kWaveSize * kWaves3), params, 0, s);
+}
+
+template <class R>
+static hipError_t launch_slab_with(const void* f, const Pass3Desc& d, bool close_only,
+                                   hipStream_t s) {
+    March3Args<R> a = {};
+    a.src = d.src;
+    a.dst = d.dst;
+    a.ptab = d.ptab;
+    a.nx = d.nx;
+    a.ny = d.ny;
+    a.nz = d.nz;
+    a.strip_sites = slab_strip(d.stages);
+    a.slab_pairs = slab_pairs(d.stages, d.rp);
+    a.seg_pairs = d.seg_pairs;
+    a.nstrips = (d.nx + a.strip_sites - 1) / a.strip_sites;
+    a.nslabs = (d.ny / 2 + a.slab_pairs - 1) / a.slab_pairs;
+    a.nsegs = (d.nz / 2 + d.seg_pairs - 1) / d.seg_pairs;
+    double Le = 0.0;  // the six even factors
+    for (int ax = 0; ax < 3; ++ax) {
+        a.t1[ax] = tangent<R>(d.oh[ax]);
+        a.t2[ax] = tangent<R>(d.o2[ax]);
+        a.o1t[ax] = d.first ? a.t1[ax] : a.t2[ax];
+        Le += 2.0 * log_sec2(a.t1[ax]);
+    }
+    // stage 0's odd x: a tangent, or the opening half factor with the rest of its
+    // step's cosines over those the table holds; the closing one carries its own
+    a.o1x[0] = a.t2[0];
+    a.o1x[1] = R(0);
+    if (d.first)
+        delta_odd_x<R>(d.oh[0].al,
+                       Le + log_sec2(a.o1t[1]) + log_sec2(a.o1t[2]) - step3_log_sec2<R>(d.oh, d.o2),
+                       a.o1x[0], a.o1x[1]);
+    delta_odd_x<R>(d.oh[0].al, log_sec2(a.t1[1]) + log_sec2(a.t1[2]), a.c1x[0], a.c1x[1]);
+    void* params[] = {&a};
+    if (close_only) {
+        const long long lines = (long long)(d.ny / 2) * (d.nz / 2);
+        return hipLaunchKernel(f, dim3((d.nx / 2 + 255) / 256, (unsigned)std::min(lines, 65535LL)),
+                               dim3(256), params, 0, s);
+    }
+    const long long tiles = (long long)a.nstrips * a.nslabs * a.nsegs;
+    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    return hipLaunchKernel(f, dim3((unsigned)tiles), dim3(kWaveSize * kWaves3), params, 0, s);
+}
+
+hipError_t launch_close3(int dtype, const Pass3Desc& d, hipStream_t s) {
+    const void* f = dtype == 1 ? close3_ptr_c128() : close3_ptr_c64();
+    if (!f) return hipErrorInvalidValue;
+    hipError_t e = dtype == 1 ? launch_slab_with<double>(f, d, true, s)
+                              : launch_slab_with<float>(f, d, true, s);
+    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_slab(int dtype, const Pass3Desc& d, hipStream_t s) {
+    const void* f = dtype == 1 ? slab_ptr_c128(d.stages, d.rp, d.close) : slab_ptr_c64(d.stages, d.rp, d.close);
+    const long long plane_bytes = (long long)d.nx * d.ny * (dtype == 1 ? 16 : 8);
+    if (!f || d.seg_pairs < 1 || plane_bytes > kMaxSlabPlane) return hipErrorInvalidValue;
+    hipError_t e = dtype == 1 ? launch_slab_with<double>(f, d, false, s)
+                              : launch_slab_with<float>(f, d, false, s);
+    if (e != hipSuccess) return e;
+    return hipGetLastError();
 }
 
 hipError_t launch_pass3(int dtype, const Pass3Desc& d, hipStream_t s) {

@@ -203,14 +203,30 @@ struct C64 {
 // numbers (scale 2^30; 8 bytes, the size of a complex64, but about 31 bits
 // per part instead of 24, so the coherent per-site error of a rounded table,
 // repeated every step, stays below 7e-10 per step); they split exactly into a
-// hi float (the top 24 bits) and a lo float (the low 7 bits), the pair the
-// complex64 phase multiply takes.
+// hi float (bits 8 and up, 23 of them with the sign apart) and a lo float (the
+// low byte, which one conversion extracts), the pair the complex64 phase
+// multiply takes.
+__device__ __forceinline__ float4 split_phase(int2 t) {
+    return make_float4((float)(t.x & ~0xff), (float)(t.y & ~0xff), (float)(unsigned char)t.x,
+                       (float)(unsigned char)t.y);
+}
 __device__ __forceinline__ double2 decode_phase(double2 t) { return t; }
 __device__ __forceinline__ float4 decode_phase(int2 t) {
     const float sc = 0x1p-30f;
-    const int hx = t.x & ~0x7f, hy = t.y & ~0x7f;
-    return make_float4((float)hx * sc, (float)hy * sc, (float)(t.x - hx) * sc,
-                       (float)(t.y - hy) * sc);
+    const float4 p = split_phase(t);
+    return make_float4(p.x * sc, p.y * sc, p.z * sc, p.w * sc);
+}
+
+// The phase multiply by a table entry as stored.  complex64: the scale 2^-30
+// comes last (two multiplies instead of four; a power of two, so the same bits
+// as apply_phase of the decoded entry unless a part of psi is beyond 1e29).
+__device__ __forceinline__ void apply_table(double& re, double& im, const double2 p) {
+    apply_phase(re, im, p);
+}
+__device__ __forceinline__ void apply_table(float& re, float& im, const int2 t) {
+    apply_phase(re, im, split_phase(t));
+    re *= 0x1p-30f;
+    im *= 0x1p-30f;
 }
 
 template <class R, int SPL>
@@ -339,6 +355,46 @@ template <class R, int SPL>
 __device__ __forceinline__ void pair_y_t(Row<R, SPL>& u, Row<R, SPL>& v, R t) {
 #pragma unroll
     for (int i = 0; i < SPL; ++i) rot_pair_t(u.re[i], u.im[i], v.re[i], v.im[i], t);
+}
+
+// Two sites of a row in 16-byte parts of LDS, one part per lane and component pair
+// (complex64: one part; complex128: two).
+__device__ __forceinline__ void put16(float4 (&v)[1][kWaveSize], int lane, const Row<float, 2>& r) {
+    v[0][lane] = make_float4(r.re[0], r.im[0], r.re[1], r.im[1]);
+}
+__device__ __forceinline__ void get16(const float4 (&v)[1][kWaveSize], int lane, Row<float, 2>& r) {
+    const float4 a = v[0][lane];
+    r.re[0] = a.x; r.im[0] = a.y;
+    r.re[1] = a.z; r.im[1] = a.w;
+}
+__device__ __forceinline__ void put16(float4 (&v)[2][kWaveSize], int lane, const Row<double, 2>& r) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        *reinterpret_cast<double2*>(&v[i][lane]) = make_double2(r.re[i], r.im[i]);
+}
+__device__ __forceinline__ void get16(const float4 (&v)[2][kWaveSize], int lane, Row<double, 2>& r) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double2 a = *reinterpret_cast<const double2*>(&v[i][lane]);
+        r.re[i] = a.x;
+        r.im[i] = a.y;
+    }
+}
+
+// Row `a` of an odd y-pair with its partner `b`, which another wavefront
+// holds: the side of pair_y_t / pair_y that belongs to `a`.
+template <class R>
+__device__ __forceinline__ void side_y_t(Row<R, 2>& a, const Row<R, 2>& b, R t) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        a.re[i] = mad(-t, b.im[i], a.re[i]);
+        a.im[i] = mad(t, b.re[i], a.im[i]);
+    }
+}
+template <class R>
+__device__ __forceinline__ void side_y(Row<R, 2>& a, const Row<R, 2>& b, R s, R d) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) rot_site(a.re[i], a.im[i], b.re[i], b.im[i], s, d);
 }
 
 // Even x-pairs in the tangent form (closed meshes: a zero tangent for a pair

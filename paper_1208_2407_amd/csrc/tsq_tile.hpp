@@ -33,44 +33,6 @@ struct TileExchange {
     float4 v[2][kTileWaves][2][kParts][kWaveSize];
 };
 
-__device__ __forceinline__ void tile_put(float4 (&v)[1][kWaveSize], int lane, const Row<float, 2>& r) {
-    v[0][lane] = make_float4(r.re[0], r.im[0], r.re[1], r.im[1]);
-}
-__device__ __forceinline__ void tile_get(const float4 (&v)[1][kWaveSize], int lane, Row<float, 2>& r) {
-    const float4 a = v[0][lane];
-    r.re[0] = a.x; r.im[0] = a.y;
-    r.re[1] = a.z; r.im[1] = a.w;
-}
-__device__ __forceinline__ void tile_put(float4 (&v)[2][kWaveSize], int lane, const Row<double, 2>& r) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-        *reinterpret_cast<double2*>(&v[i][lane]) = make_double2(r.re[i], r.im[i]);
-}
-__device__ __forceinline__ void tile_get(const float4 (&v)[2][kWaveSize], int lane, Row<double, 2>& r) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const double2 a = *reinterpret_cast<const double2*>(&v[i][lane]);
-        r.re[i] = a.x;
-        r.im[i] = a.y;
-    }
-}
-
-// Row `a` of an odd y-pair with its partner `b`, which another wavefront
-// holds: the side of pair_y_t / pair_y that belongs to `a`.
-template <class R>
-__device__ __forceinline__ void side_y_t(Row<R, 2>& a, const Row<R, 2>& b, R t) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        a.re[i] = mad(-t, b.im[i], a.re[i]);
-        a.im[i] = mad(t, b.re[i], a.im[i]);
-    }
-}
-template <class R>
-__device__ __forceinline__ void side_y(Row<R, 2>& a, const Row<R, 2>& b, R s, R d) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) rot_site(a.re[i], a.im[i], b.re[i], b.im[i], s, d);
-}
-
 // One pass of `a.tile_steps` steps (plus the closing odd factors if `a.tile_last`)
 // over one strip and segment (a.seg_rows = 2 (T - 2K) stored rows).
 template <class T, int RP, bool CLOSED, bool TD, bool U4>
@@ -217,16 +179,16 @@ tile_kernel(const MarchArgs<typename T::R> a) {
                     odd_x_t(h[j].g, oxs);
                 }
             }
-            tile_put(xch.v[buf][w][0], lane, h[0].f);
-            tile_put(xch.v[buf][w][1], lane, h[RP - 1].g);
+            put16(xch.v[buf][w][0], lane, h[0].f);
+            put16(xch.v[buf][w][1], lane, h[RP - 1].g);
         }
         // one barrier a step: a buffer is written again two steps later, after
         // the barrier that every wavefront meets once it has read it
         __syncthreads();
         if (p0 + RP - 1 <= k || p0 >= NT - 1 - k) continue;  // completes no pair
         Row<R, 2> up{}, dn{};  // bottom row of the pair above, top row of the pair below
-        if (w > 0) tile_get(xch.v[buf][w - 1][1], lane, up);
-        if (w + 1 < kTileWaves) tile_get(xch.v[buf][w + 1][0], lane, dn);
+        if (w > 0) get16(xch.v[buf][w - 1][1], lane, up);
+        if (w + 1 < kTileWaves) get16(xch.v[buf][w + 1][0], lane, dn);
         if constexpr (CLOSED) {
             // odd y-pair of pairs q and q+1: rows 2q+1, 2q+2
             auto oy = [&](int q) { return q >= 0 && 2 * q + 2 < ny; };
