@@ -94,10 +94,7 @@ constexpr size_t kScratchBytes = (2 * tsq::kReduceBlocks + 2) * sizeof(double);
 
 // Default schedule.  Steps per pass: 5 with the register phase ring (within a
 // few percent of the fastest schedule for both dtypes at 4096^2).  Segment
-// height: as many wavefront tiles as the device holds resident at once (one
-// round, no tail of a partly filled second round) while segments of at least
-// 2K row pairs keep the discarded warm-up pairs below half the work; smaller
-// meshes: see default_seg_rows.
+// height: see default_seg_rows.
 constexpr int kDefaultSteps = 5;
 
 // Fill the zero fields of a requested schedule with defaults; false if the
@@ -148,45 +145,43 @@ int occupancy_cached(int dtype, int steps, bool last, int ppl, bool lds, bool cl
     return v;
 }
 
+// Rows per segment of a pass whose schedule leaves them to the library.
+// One round of resident blocks, at most two per compute unit for complex64 and
+// one for complex128: more wavefronts hide no more latency there, and every
+// segment reads 2K row pairs of halo (4096^2 complex64 at 2 steps per pass: 65.6
+// us with two blocks a unit, 69.8 with four; 2048^2 complex128 fourth order 54
+// with one, 67 with two).
+// A mesh too small for segments of 2K pairs that way: a pass lasts as long as
+// its busiest SIMD, which marches its wavefronts' Q + K pairs (the pipeline's
+// fill skipped) one behind the other, each pair 0.22 us a step alone (complex64)
+// and 0.78 of that per wavefront when several share the SIMD (complex128 0.95).
+// The height with the least of that: 1030 x 614 complex64 at 5 steps per pass
+// takes 8 rows, 13.9 us a pass against 20.8 at 2K pairs (6 rows, two blocks on
+// some units: 17.3); 256^2 takes 2 rows, 10.1 against 18.9 us.
 int default_seg_rows(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool closed,
                      bool td, bool u4 = false) {
     const tsq::MarchGeometry g = tsq::march_geometry(p->p.nx, p->p.ny, steps, last, ppl, 2);
     int cus = device_cus();
     if (cus <= 0) cus = 256;
-    const long long slots =
-        (long long)cus * occupancy_cached(p->p.dtype, steps, last, ppl, lds, closed, td, u4) *
-        tsq::kWavesPerBlock;
-    const long long pairs = (p->p.ny + 1) / 2;
+    const bool c128 = p->p.dtype == TSQ_C128;
+    const int occ = occupancy_cached(p->p.dtype, steps, last, ppl, lds, closed, td, u4);
+    const long long pairs = (p->p.ny + 1) / 2, K = steps + (last ? 1 : 0);
     // a launch has one block per segment of kWavesPerBlock strips
-    const long long strip_slots =
-        (g.nstrips + tsq::kWavesPerBlock - 1) / tsq::kWavesPerBlock * tsq::kWavesPerBlock;
-    long long segs = slots / strip_slots;
-    if (segs < 1) segs = 1;
-    if (segs > pairs) segs = pairs;
-    long long pairs_per_seg = (pairs + segs - 1) / segs;
-    const long long K = steps + (last ? 1 : 0);
-    if (pairs_per_seg >= 2 * K) return (int)(2 * pairs_per_seg);
-    // A mesh too small for segments of 2K pairs in one round: a pass lasts as
-    // long as its busiest SIMD, which marches its wavefronts' Q + K pairs (the
-    // pipeline's fill skipped) one behind the other, each pair 0.22 us a step
-    // alone (complex64, 1 wavefront per SIMD) and about 0.85 of that per
-    // wavefront when two or more share the SIMD.  The height with the least of
-    // that, a block of kWavesPerBlock wavefronts per compute unit: 1030 x 614
-    // complex64 at 5 steps per pass takes 8 rows, 13.9 us a pass against 20.8 at
-    // 2K pairs (6 rows, two blocks on some units: 17.3); 256^2 takes 2 rows,
-    // 10.1 against 18.9 us.
-    const long long groups = strip_slots / tsq::kWavesPerBlock;
+    const long long groups = (g.nstrips + tsq::kWavesPerBlock - 1) / tsq::kWavesPerBlock;
+    const long long segs = std::max(1LL, (long long)cus * std::min(occ, c128 ? 1 : 2) / groups);
+    long long q = (pairs + segs - 1) / segs;
+    if (q >= 2 * K) return (int)(2 * q);
+    const double share = c128 ? 0.95 : 0.78;
     double best = 0.0;
-    for (long long q = 1; q <= 2 * K; ++q) {
-        const long long blocks = groups * ((pairs + q - 1) / q);
-        const long long per_cu = (blocks + cus - 1) / cus;
-        const double cost = (double)(q + K) * std::max(1.0, 0.85 * (double)per_cu);
-        if (q == 1 || cost < best) {
+    for (long long t = 1; t <= 2 * K; ++t) {
+        const long long per_cu = (groups * ((pairs + t - 1) / t) + cus - 1) / cus;
+        const double cost = (double)(t + K) * std::max(1.0, share * (double)per_cu);
+        if (t == 1 || cost < best) {
             best = cost;
-            pairs_per_seg = q;
+            q = t;
         }
     }
-    return (int)(2 * pairs_per_seg);
+    return (int)(2 * q);
 }
 
 // Fourth order on a periodic 2D mesh runs one pass per fourth-order step (its
@@ -338,7 +333,8 @@ TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
     const int rows0 = default_seg_rows(p, S0, false, 1, lds0, closed, td, u4);
     const tsq::MarchGeometry g0 = tsq::march_geometry(p->p.nx, p->p.ny, S0, false, 1, rows0);
     const int64_t n0 = (g0.blocks + cus - 1) / cus;
-    const double march = launch + 0.22 * S0 * (rows0 / 2 + S0) * std::max(1.0, 0.85 * (double)n0);
+    const double march = launch + 0.22 * S0 * (rows0 / 2 + S0) *
+                                      std::max(1.0, (p->p.dtype == TSQ_C128 ? 0.95 : 0.78) * (double)n0);
     double cost = march * (u4 ? (double)steps : std::ceil((double)steps / S0));
     for (int rp = 1; rp <= (u4 ? 1 : 2); ++rp) {
         const int most = tsq::kTileWaves * rp / 2 - 1;  // stages that leave a pair to store

@@ -235,7 +235,10 @@ struct Row {
     R im[SPL];
 };
 
-// Load / store one x-pair (2 sites starting at even column `x`) of row `r`.
+// Load / store one x-pair (2 sites starting at even column `x`) of row `r`.  The
+// march gives them the row's (wavefront-uniform) address and the lane's byte
+// offset within it: the scalar unit steps the address and a load takes no vector
+// instruction but itself.
 template <int SPL>
 __device__ __forceinline__ void load_pair(const void* base, long long off, Row<double, SPL>& row, int p) {
     const double2* q = reinterpret_cast<const double2*>(base) + off;
@@ -670,7 +673,12 @@ using PhaseT = std::conditional_t<TD, double2, typename T::PT>;
 template <class T, bool TD>
 using TableT = std::conditional_t<TD, double2, typename T::TT>;
 
-template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4>
+// UA (complex64, one problem, static, second order): rows are addressed by
+// the scalar unit, see load_pair.  At 32768^2 the 6-step pass, bound by its
+// vector instructions, takes 5.6% less time; the marches bound by memory and the
+// batched one, whose row addresses come from a job record, run 1 to 2% slower
+// that way and keep per-lane addresses.
+template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4, bool UA>
 __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, int strip, int seg,
                                            bool rev, int lane, PhaseT<T, TD>* ring,
                                            const double2* turns) {
@@ -732,6 +740,22 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
         const long long x = xu0 + i;
         ccol[i] = CLOSED ? (int)(x < 0 ? 0 : (x >= nx ? nx - 1 : x)) : 0;
     }
+    // UA: bytes of a row, the lane's offset within it (psi and the complex64
+    // table have 8 bytes a site both)
+    const long long rbytes = (long long)nx * (2 * sizeof(R));
+    unsigned loff[PPL];
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) loff[p] = (unsigned)col[p] * (unsigned)(2 * sizeof(R));
+    // A new value of the same offset in the block of the accesses: the compiler
+    // folds a 32-bit lane offset into an access only if it widens it right there.
+    auto fresh = [](unsigned (&o)[PPL]) {
+        if constexpr (UA) {
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) asm volatile("" : "+v"(o[p]));
+        } else {
+            (void)o;
+        }
+    };
     auto clamp_row = [&](int r) { return r < 0 ? 0 : (r >= ny ? ny - 1 : r); };
 
     // y: output row pairs [q0, q1); input pairs [q0 - K, q1 - 1 + K], visited in
@@ -768,6 +792,10 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
             const long long off = (long long)clamp_row(r) * nx;
 #pragma unroll
             for (int i = 0; i < SPL; ++i) load_site(a.src, off + ccol[i], w.re[i], w.im[i]);
+        } else if constexpr (UA) {
+            const char* base = static_cast<const char*>(a.src) + r * rbytes;
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) load_pair(base + loff[p], 0, w, p);
         } else {
             const long long off = (long long)r * nx;
 #pragma unroll
@@ -775,6 +803,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
         }
     };
     auto load_psi = [&](PairRows<R, SPL>& h) {
+        fresh(loff);
         load_row(rpsi + fo, h.f);
         load_row(rpsi + 1 - fo, h.g);
         step_row(rpsi);
@@ -785,6 +814,15 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
             const long long off = (long long)clamp_row(r) * nx;
 #pragma unroll
             for (int i = 0; i < SPL; ++i) v[i] = decode_phase(P[off + ccol[i]]);
+        } else if constexpr (UA) {
+            static_assert(!UA || sizeof(TableT<T, TD>) == 2 * sizeof(R), "psi and table sites of one size");
+            const char* base = static_cast<const char*>(a.ptab) + r * rbytes;
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) {
+                const TableT<T, TD>* q = reinterpret_cast<const TableT<T, TD>*>(base + loff[p]);
+                v[2 * p] = decode_phase(q[0]);
+                v[2 * p + 1] = decode_phase(q[1]);
+            }
         } else {
             const long long off = (long long)r * nx;
 #pragma unroll
@@ -795,6 +833,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
         }
     };
     auto load_phase = [&](PhasePair<PT, SPL>& ph) {
+        fresh(loff);
         load_phase_row(rph + fo, ph.f);
         load_phase_row(rph + 1 - fo, ph.g);
         step_row(rph);
@@ -827,6 +866,17 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
                 if (inner && site_ok[i]) {
                     if (rf < ny) store_site(a.dst, rf * nx + xu0 + i, h.f.re[i], h.f.im[i]);
                     if (rg < ny) store_site(a.dst, rg * nx + xu0 + i, h.g.re[i], h.g.im[i]);
+                }
+            }
+        } else if constexpr (UA) {
+            fresh(loff);
+            char* bf = static_cast<char*>(a.dst) + rf * rbytes;
+            char* bg = static_cast<char*>(a.dst) + rg * rbytes;
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) {
+                if (keep[p]) {
+                    store_pair(bf + loff[p], 0, h.f, p);
+                    store_pair(bg + loff[p], 0, h.g, p);
                 }
             }
         } else {
@@ -965,7 +1015,8 @@ march_kernel(const MarchArgs<typename T::R> a) {
     const int grp = lb - seg * ngroups;
     const int strip = grp * kWavesPerBlock + wave;
     if (strip >= a.nstrips) return;  // uniform per wavefront
-    march_tile<T, S, LAST, PPL, LDS, CLOSED, TD, U4>(a, strip, seg, seg & 1, lane,
+    constexpr bool UA = sizeof(typename T::R) == 4 && !CLOSED && !TD && !U4;
+    march_tile<T, S, LAST, PPL, LDS, CLOSED, TD, U4, UA>(a, strip, seg, seg & 1, lane,
                                                  &rings[LDS ? wave : 0].v[0][0][0][lane], turns);
 }
 
@@ -983,7 +1034,7 @@ march_batch_kernel(const MarchArgs<typename T::R>* __restrict__ jobs,
     for (int i = blockIdx.x * kWavesPerBlock + wave; i < ntiles; i += nw) {
         const BatchTile t = tiles[i];
         const MarchArgs<typename T::R> a = jobs[t.job];
-        march_tile<T, S, LAST, PPL, LDS, false, false, false>(a, t.strip, t.seg, t.seg & 1, lane,
+        march_tile<T, S, LAST, PPL, LDS, false, false, false, false>(a, t.strip, t.seg, t.seg & 1, lane,
                                                        &rings[LDS ? wave : 0].v[0][0][0][lane],
                                                        nullptr);
     }
