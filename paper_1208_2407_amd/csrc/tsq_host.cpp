@@ -424,34 +424,84 @@ size_t blob_reserve(std::vector<unsigned char>& blob, size_t bytes) {
     return off;
 }
 
+// Tile height of one launch of a batch whose schedule leaves it to the library.
+// A launch lasts as long as its busiest SIMD.  One round: the lowest height whose
+// tiles fit n blocks of wavefronts per compute unit, n = 1 .. occupancy, each SIMD
+// marching the tallest tile's Q + K pairs per wavefront (see default_seg_rows).
+// Several rounds, at a few heights that give them: the tiles' pairs shared evenly and a sixth of
+// a tile for the tail of the walk (a third picks one round for the 200 below, 1974).
+// The least of these; us per call before (all strips stacked over the resident
+// wavefronts, never under 2K pairs: a few hundred wavefronts walked a second tile)
+// and after, complex64 unless said, problems of sides 64 to 1024 and 100 steps
+// unless said: 3 of 64 to 512 in complex128, 60 steps, 286 and 170; 8 of 64 to 256,
+// 451 and 266; 48, 1320 and 1282; 48 in complex128, 2191 and 1929; 16 of 128 to
+// 4096, 20 steps, 993 and 895; 200, 40 steps, 1930 to 1977 and 1924; 512, 40 steps,
+// 4057 to 4081 and 4077 to 4103.
+long long tile_rows(const tsq_batch* b, const std::vector<tsq::PassDesc>& descs, int steps, bool last,
+                    int cus, int slots) {
+    const int ppl = b->sched.pairs_per_lane;
+    const long long K = steps + (last ? 1 : 0);
+    std::vector<std::pair<long long, long long>> dims;  // (strips, rows) per problem
+    long long strip_rows = 0, tallest = 2;
+    for (const tsq::PassDesc& d : descs) {
+        const long long st = tsq::march_geometry(d.nx, d.ny, steps, last, ppl, 2).nstrips;
+        dims.emplace_back(st, d.ny);
+        strip_rows += st * d.ny;
+        tallest = std::max<long long>(tallest, d.ny);
+    }
+    auto count = [&](long long h) {
+        long long n = 0;
+        for (const auto& x : dims) n += x.first * ((x.second + h - 1) / h);
+        return n;
+    };
+    const double share = b->dtype == TSQ_C128 ? 0.95 : 0.78;
+    const long long round = (long long)cus * tsq::kWavesPerBlock;
+    long long h = 2;
+    double best = 0.0;
+    auto consider = [&](long long rows, double pairs, double per_simd) {
+        const double cost = pairs * std::max(1.0, share * per_simd);
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            h = rows;
+        }
+    };
+    for (long long n = 1; n * round <= slots; ++n) {
+        const long long waves = n * round;
+        if (count(tallest) > waves) continue;
+        long long lo = 1, hi = (tallest + 1) / 2;  // in row pairs: hi fits
+        while (lo < hi) {
+            const long long mid = (lo + hi) / 2;
+            if (count(2 * mid) <= waves)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        consider(2 * lo, (double)(lo + K), (double)n);
+    }
+    for (long long rows = 64; rows <= 512 && count(rows) > slots; rows *= 2)
+        consider(rows, (0.5 * (double)strip_rows + (double)(K * count(rows))) / (double)slots +
+                           (double)(rows / 2 + K) / 6.0,
+                 (double)slots / (double)round);
+    return h;
+}
+
 template <class R>
 void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::PassDesc>& descs,
-                   int slots) {
+                   int cus, int slots) {
     const int ppl = b->sched.pairs_per_lane;
-    const int K = steps + (last ? 1 : 0);
-    // Tile height: the schedule's segment_rows if set; else the strips of all
-    // problems stacked, cut into about one tile per resident wavefront, never
-    // shorter than 2K row pairs.
-    long long h = b->sched.segment_rows;
-    if (h <= 0) {
-        long long strip_rows = 0;
-        for (const tsq::PassDesc& d : descs)
-            strip_rows +=
-                (long long)tsq::march_geometry(d.nx, d.ny, steps, last, ppl, 2).nstrips * d.ny;
-        h = (strip_rows + slots - 1) / slots;
-        if (h < 4LL * K) h = 4LL * K;
-        h = (h + 1) & ~1LL;
-    }
-
-    std::vector<tsq::MarchArgs<R>> jobs;
+    const long long h = b->sched.segment_rows > 0 ? b->sched.segment_rows
+                                                  : tile_rows(b, descs, steps, last, cus, slots);
+    std::vector<tsq::BatchJob<R>> jobs;
     std::vector<tsq::BatchTile> tiles;
     for (size_t j = 0; j < descs.size(); ++j) {
         tsq::PassDesc d = descs[j];
         d.seg_rows = (int)std::min<long long>(h, d.ny);
         const tsq::MarchGeometry g = tsq::march_geometry(d.nx, d.ny, steps, last, ppl, d.seg_rows);
-        jobs.push_back(tsq::make_march_args<R>(d, g));
-        for (int st = 0; st < g.nstrips; ++st)
-            for (int sg = 0; sg < g.nsegs; ++sg) {
+        jobs.push_back(tsq::batch_job(tsq::make_march_args<R>(d, g)));
+        // neighbouring strips of a segment next to each other: a block's
+        // wavefronts read the halo columns they share at about the same time
+        for (int sg = 0; sg < g.nsegs; ++sg)
+            for (int st = 0; st < g.nstrips; ++st) {
                 const int rows = std::min(d.seg_rows, d.ny - sg * d.seg_rows);
                 tiles.push_back(tsq::BatchTile{(int)j, st, sg, rows});
             }
@@ -464,10 +514,22 @@ void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::Pa
     L.njobs = (int)jobs.size();
     L.ntiles = (int)tiles.size();
     L.nwaves = std::min(L.ntiles, slots);
-    L.jobs_off = blob_reserve(b->blob, jobs.size() * sizeof(tsq::MarchArgs<R>));
-    std::memcpy(b->blob.data() + L.jobs_off, jobs.data(), jobs.size() * sizeof(tsq::MarchArgs<R>));
-    L.tiles_off = blob_reserve(b->blob, tiles.size() * sizeof(tsq::BatchTile));
-    std::memcpy(b->blob.data() + L.tiles_off, tiles.data(), tiles.size() * sizeof(tsq::BatchTile));
+    L.jobs_off = blob_reserve(b->blob, jobs.size() * sizeof(tsq::BatchJob<R>));
+    std::memcpy(b->blob.data() + L.jobs_off, jobs.data(), jobs.size() * sizeof(tsq::BatchJob<R>));
+    // the steady passes of a batch walk the same tiles: one copy serves them all
+    const size_t bytes = tiles.size() * sizeof(tsq::BatchTile);
+    bool shared = false;
+    for (size_t i = b->launches.size(); i-- > 0 && !shared;) {
+        const BatchLaunch& o = b->launches[i];
+        if (o.steps != steps || o.last != last) continue;
+        shared = o.ntiles == L.ntiles && std::memcmp(b->blob.data() + o.tiles_off, tiles.data(), bytes) == 0;
+        L.tiles_off = o.tiles_off;
+        break;
+    }
+    if (!shared) {
+        L.tiles_off = blob_reserve(b->blob, bytes);
+        std::memcpy(b->blob.data() + L.tiles_off, tiles.data(), bytes);
+    }
     b->launches.push_back(L);
     b->total_tiles += L.ntiles;
 }
@@ -584,9 +646,9 @@ int tsq_batch_create(tsq_plan* const* plans, void* const* psi, void* const* ws, 
             if (bpc <= 0) bpc = 1;
             const int slots = cus * bpc * tsq::kWavesPerBlock;
             if (dtype == TSQ_C128)
-                append_launch<double>(b, st, last, kv.second, slots);
+                append_launch<double>(b, st, last, kv.second, cus, slots);
             else
-                append_launch<float>(b, st, last, kv.second, slots);
+                append_launch<float>(b, st, last, kv.second, cus, slots);
         }
     }
     *out = b;

@@ -67,8 +67,7 @@ MarchGeometry march_geometry(int nx, int ny, int steps, bool last, int pairs_per
 // segments of 2 (kTileWaves rp - 2K) rows, one block per strip and segment.
 MarchGeometry tile_geometry(int nx, int ny, int steps, bool last, int rp);
 
-// Kernel arguments of one pass over one problem (also the job record of the
-// batched kernel, uploaded to device memory).  R = double (complex128) or
+// Kernel arguments of one pass over one problem.  R = double (complex128) or
 // float (complex64).
 //
 // Two forms of the rotations: the delta form a' = a + (i s b - d a) (4
@@ -244,6 +243,36 @@ MarchArgs<R> make_march_args(const PassDesc& d, const MarchGeometry& g) {
     return a;
 }
 
+// Job record of the batched kernel, uploaded to device memory: the launch
+// arguments a periodic static second-order pass uses.  Its size decides which
+// batches fit tsq_batch_evolve_noalloc's fixed array, so it stays what it was when
+// it held a whole MarchArgs (kJobBytes).
+template <class R>
+constexpr size_t kJobBytes = sizeof(R) == 4 ? 288 : 440;
+template <class R>
+struct BatchJob {
+    const void* src;
+    void* dst;
+    const void* ptab;
+    int nx, ny, strip_sites, seg_rows, nstrips, nsegs;
+    R o1xs, o1xd, o1ys, o2xs, o2ys, ehxs, ehys, c1xs, c1xd, c1ys;
+    unsigned char unused[kJobBytes<R> - 3 * 8 - 6 * 4 - 10 * sizeof(R)];
+};
+static_assert(sizeof(BatchJob<float>) == kJobBytes<float> && sizeof(BatchJob<double>) == kJobBytes<double>,
+              "job records of the stated size");
+template <class R>
+BatchJob<R> batch_job(const MarchArgs<R>& a) {
+    BatchJob<R> j = {};
+    j.src = a.src; j.dst = a.dst; j.ptab = a.ptab;
+    j.nx = a.nx; j.ny = a.ny; j.strip_sites = a.strip_sites; j.seg_rows = a.seg_rows;
+    j.nstrips = a.nstrips; j.nsegs = a.nsegs;
+    j.o1xs = a.o1xs; j.o1xd = a.o1xd; j.o1ys = a.o1ys;
+    j.o2xs = a.o2xs; j.o2ys = a.o2ys;
+    j.ehxs = a.ehxs; j.ehys = a.ehys;
+    j.c1xs = a.c1xs; j.c1xd = a.c1xd; j.c1ys = a.c1ys;
+    return j;
+}
+
 // One entry of the batched kernel's work list.
 struct BatchTile {
     int job;    // index into the launch's MarchArgs array
@@ -289,7 +318,7 @@ hipError_t launch_tile(int dtype, const PassDesc& d, int rp, hipStream_t s);
 hipError_t launch_observables_final(const double* partial, int nblocks, double* result,
                                     hipStream_t s);
 // Batched pass: `nwaves` wavefronts walk `ntiles` tiles of `jobs` (device
-// MarchArgs<double> for complex128, MarchArgs<float> for complex64).
+// BatchJob<double> for complex128, BatchJob<float> for complex64).
 hipError_t launch_batch(int dtype, int steps, bool last, int pairs_per_lane, bool phase_lds,
                         const void* jobs, const BatchTile* tiles, int ntiles, int nwaves,
                         hipStream_t s);

@@ -1025,7 +1025,7 @@ march_kernel(const MarchArgs<typename T::R> a) {
 // host sorts the list by tile height so the strided walk balances the load.
 template <class T, int S, bool LAST, int PPL, bool LDS>
 __global__ void __launch_bounds__(kWaveSize * kWavesPerBlock)
-march_batch_kernel(const MarchArgs<typename T::R>* __restrict__ jobs,
+march_batch_kernel(const BatchJob<typename T::R>* __restrict__ jobs,
                    const BatchTile* __restrict__ tiles, int ntiles) {
     __shared__ WaveRing<typename T::PT, S, PPL, LDS> rings[LDS ? kWavesPerBlock : 1];
     const int lane = threadIdx.x & (kWaveSize - 1);
@@ -1033,7 +1033,14 @@ march_batch_kernel(const MarchArgs<typename T::R>* __restrict__ jobs,
     const int nw = gridDim.x * kWavesPerBlock;
     for (int i = blockIdx.x * kWavesPerBlock + wave; i < ntiles; i += nw) {
         const BatchTile t = tiles[i];
-        const MarchArgs<typename T::R> a = jobs[t.job];
+        const BatchJob<typename T::R>& j = jobs[t.job];
+        MarchArgs<typename T::R> a = {};
+        a.src = j.src; a.dst = j.dst; a.ptab = j.ptab;
+        a.nx = j.nx; a.ny = j.ny; a.strip_sites = j.strip_sites; a.seg_rows = j.seg_rows;
+        a.o1xs = j.o1xs; a.o1xd = j.o1xd; a.o1ys = j.o1ys;
+        a.o2xs = j.o2xs; a.o2ys = j.o2ys;
+        a.ehxs = j.ehxs; a.ehys = j.ehys;
+        a.c1xs = j.c1xs; a.c1xd = j.c1xd; a.c1ys = j.c1ys;
         march_tile<T, S, LAST, PPL, LDS, false, false, false, false>(a, t.strip, t.seg, t.seg & 1, lane,
                                                        &rings[LDS ? wave : 0].v[0][0][0][lane],
                                                        nullptr);
