@@ -4,6 +4,8 @@
 
 #include "tsq_internal.h"
 
+#include <algorithm>
+
 namespace tsq {
 namespace {
 
@@ -12,6 +14,13 @@ struct C64 {};
 
 // ------------------------------------------------------------------ phase table of H0 (Sec. 2)
 
+// Bound by FP64 arithmetic with the library's sincos (its long reduction above all),
+// by memory with the short one below: complex64 us, before and now, 2048 x 1024
+// 16.9 and 9.7, 3000 x 2000 30.1 and 21.4, 4096^2 87.5 and 55.1 (268 MB read and
+// written: 4.9 TB/s), 16384 x 8192 546 and 458; complex128 (the library's, whose
+// last bits its table keeps) 2048 x 1024 18.0 and 12.2, 3000 x 2000 31.9 and 25.0,
+// 4096^2 103 and 85, from the grid alone (see launch_phase_table).
+//
 // exp(-i phi_l) times the site's scale (the cosines the march's tangent-form
 // factors leave out; see TableScale) for sites l = i, i + n/4... of each
 // thread's four-site groups: the four loads of V are issued before the four
@@ -22,32 +31,75 @@ __device__ __forceinline__ double site_scale(const TableScale& sc, long long l) 
     const bool y = sc.wy0 >= 0 && l >= sc.wy0;
     return x ? (y ? sc.gxy : sc.gx) : (y ? sc.gy : sc.g);
 }
-template <class Store>
+// sin and cos for a table that rounds to 2^-31: x = j pi/2 + r with j the integer
+// nearest x 2/pi, |r| <= pi/4, pi/2 in two parts (the first product is exact in its
+// FMA), then the Taylor series of sin r through r^15 and cos r through r^16 (omitted
+// below 4.7e-17 and 2.1e-18).  j comes from adding 1.5 * 2^52 in the FMA that forms
+// x 2/pi, so the low bits of the sum hold it.  Within 1.5e-16 of the exact values
+// for |x| < 2^30; larger angles, infinities and NaN take the library's.
+__device__ __forceinline__ void sincos_table(double x, double* s, double* c) {
+    if (!(fabs(x) < 0x1p30)) {
+        sincos(x, s, c);
+        return;
+    }
+    const double shifter = 0x1.8p52;
+    const double t = __builtin_fma(x, 0x1.45f306dc9c883p-1, shifter);  // 2/pi
+    const double j = t - shifter;
+    const int q = __double2loint(t);
+    double r = __builtin_fma(-j, 0x1.921fb54442d18p+0, x);  // pi/2 rounded, and the rest
+    r = __builtin_fma(-j, 0x1.1a62633145c07p-54, r);
+    const double z = r * r;
+    double a = -1.0 / 1307674368000.0;  // sin r = r + r z a
+    a = __builtin_fma(a, z, 1.0 / 6227020800.0);
+    a = __builtin_fma(a, z, -1.0 / 39916800.0);
+    a = __builtin_fma(a, z, 1.0 / 362880.0);
+    a = __builtin_fma(a, z, -1.0 / 5040.0);
+    a = __builtin_fma(a, z, 1.0 / 120.0);
+    a = __builtin_fma(a, z, -1.0 / 6.0);
+    const double sn = __builtin_fma(r * z, a, r);
+    double b = 1.0 / 20922789888000.0;  // cos r = 1 + z b
+    b = __builtin_fma(b, z, -1.0 / 87178291200.0);
+    b = __builtin_fma(b, z, 1.0 / 479001600.0);
+    b = __builtin_fma(b, z, -1.0 / 3628800.0);
+    b = __builtin_fma(b, z, 1.0 / 40320.0);
+    b = __builtin_fma(b, z, -1.0 / 720.0);
+    b = __builtin_fma(b, z, 1.0 / 24.0);
+    b = __builtin_fma(b, z, -0.5);
+    const double cs = __builtin_fma(b, z, 1.0);
+    const double sv = (q & 1) ? cs : sn, cv = (q & 1) ? sn : cs;
+    *s = (q & 2) ? -sv : sv;
+    *c = ((q + 1) & 2) ? -cv : cv;
+}
+
+template <bool TABLE, class Store>
 __device__ __forceinline__ void phase_sites(const double* __restrict__ V, long long n, double dt,
                                             double eps0, double hbar, Store&& store) {
     const long long stride = (long long)gridDim.x * blockDim.x;
     long long l = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    auto phase = [&](double v, long long at) {
+        double s, c;
+        const double x = dt * (v + eps0) / hbar;
+        if constexpr (TABLE)
+            sincos_table(x, &s, &c);
+        else
+            sincos(x, &s, &c);
+        store(at, c, s);
+    };
     for (; l + 3 * stride < n; l += 4 * stride) {
         double v[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = V[l + k * stride];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            double s, c;
-            sincos(dt * (v[k] + eps0) / hbar, &s, &c);
-            store(l + k * stride, c, s);
+            phase(v[k], l + k * stride);
         }
     }
-    for (; l < n; l += stride) {
-        double s, c;
-        sincos(dt * (V[l] + eps0) / hbar, &s, &c);
-        store(l, c, s);
-    }
+    for (; l < n; l += stride) phase(V[l], l);
 }
 
 __global__ void phase_table_c128(const double* __restrict__ V, double2* __restrict__ P,
                                  long long n, double dt, double eps0, double hbar, TableScale sc) {
-    phase_sites(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
+    phase_sites<false>(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
         const double g = site_scale(sc, l);
         P[l] = make_double2(g * c, -(g * s));
     });
@@ -57,7 +109,7 @@ __global__ void phase_table_c128(const double* __restrict__ V, double2* __restri
 // rounded to nearest (|value| <= 1, so 2^30 fits; error <= 2^-31 per part).
 __global__ void phase_table_c64(const double* __restrict__ V, int2* __restrict__ P,
                                 long long n, double dt, double eps0, double hbar, TableScale sc) {
-    phase_sites(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
+    phase_sites<true>(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
         const double g = site_scale(sc, l);
         P[l] = make_int2(__double2int_rn(g * c * 0x1p30), __double2int_rn(-(g * s) * 0x1p30));
     });
@@ -343,7 +395,13 @@ hipError_t launch_phase_table(int dtype, const double* V, void* ptab, long long 
                               double dt, double eps0, double hbar, const TableScale& scale,
                               hipStream_t s) {
     const int threads = 256;
+    // four sites a thread, their loads in flight together, once that leaves every
+    // compute unit 8 blocks (a round of resident wavefronts); one a thread below,
+    // where latency counts and the wavefronts hide it (one a thread up to 8192
+    // blocks: two or three loads in turn at 4M sites and more)
+    const long long round = 2048;
     long long want = (sites + threads - 1) / threads;
+    want = want <= round ? want : std::max(round, (want + 3) / 4);
     const int blocks = (int)(want < 8192 ? want : 8192);
     if (dtype == 1)
         hipLaunchKernelGGL(phase_table_c128, dim3(blocks), dim3(threads), 0, s, V,
