@@ -365,27 +365,45 @@ observables_pairs(const void* __restrict__ psi, const double* __restrict__ V, in
     }
 }
 
-__global__ void __launch_bounds__(kReduceThreads)
-observables_final(const double* __restrict__ partial, int nblocks, double* __restrict__ result) {
-    __shared__ double sn[kReduceThreads], se[kReduceThreads];
+// One block sums the partial sums, four loads in flight a thread: latency alone
+// bounds it (256 threads with one load in flight took 8.9 us for 8192 partial
+// sums; a call at 3000 x 2000, complex64, 59.4 then and 54.8 with this).
+constexpr int kFinalThreads = 1024;
+constexpr int kObservableItems = 1024;  // work items of a 2D mesh's sums (launch_observables)
+__global__ void __launch_bounds__(kFinalThreads)
+observables_final(const double2* __restrict__ partial, int nblocks, double* __restrict__ result) {
+    __shared__ double sn[kFinalThreads / kWaveSize], se[kFinalThreads / kWaveSize];
     double an = 0.0, ae = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-        an += partial[2 * b];
-        ae += partial[2 * b + 1];
-    }
-    sn[threadIdx.x] = an;
-    se[threadIdx.x] = ae;
-    __syncthreads();
-    for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            sn[threadIdx.x] += sn[threadIdx.x + w];
-            se[threadIdx.x] += se[threadIdx.x + w];
+    for (int b = threadIdx.x; b < nblocks; b += 4 * kFinalThreads) {
+        double2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = b + k * kFinalThreads;
+            v[k] = i < nblocks ? partial[i] : make_double2(0.0, 0.0);
         }
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            an += v[k].x;
+            ae += v[k].y;
+        }
     }
+    const int lane = threadIdx.x & (kWaveSize - 1), wave = threadIdx.x / kWaveSize;
+    for (int w = kWaveSize / 2; w > 0; w >>= 1) {
+        an += __shfl_down(an, w);
+        ae += __shfl_down(ae, w);
+    }
+    if (lane == 0) {
+        sn[wave] = an;
+        se[wave] = ae;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        result[0] = sn[0];
-        result[1] = sn[0] > 0.0 ? se[0] / sn[0] : 0.0;
+        for (int i = 1; i < kFinalThreads / kWaveSize; ++i) {
+            an += sn[i];
+            ae += se[i];
+        }
+        result[0] = an;
+        result[1] = an > 0.0 ? ae / an : 0.0;
     }
 }
 
@@ -429,8 +447,8 @@ hipError_t launch_td_table(const double* V0, const double* W, void* table, void*
 
 hipError_t launch_observables_final(const double* partial, int nblocks, double* result,
                                     hipStream_t s) {
-    hipLaunchKernelGGL(observables_final, dim3(1), dim3(kReduceThreads), 0, s, partial, nblocks,
-                       result);
+    hipLaunchKernelGGL(observables_final, dim3(1), dim3(kFinalThreads), 0, s,
+                       reinterpret_cast<const double2*>(partial), nblocks, result);
     return hipGetLastError();
 }
 
@@ -444,9 +462,14 @@ hipError_t launch_observables(int dtype, const void* psi, const double* V, int n
                          reinterpret_cast<uintptr_t>(V) % 16 == 0;
     const bool pairs = !closed && (nx % 2) == 0 && aligned;
     const int width = pairs ? 2 * kReduceThreads : kReduceThreads;
-    // bands of rows sized so the work items fill `nblocks` blocks once
+    // bands of rows sized so there are about kObservableItems work items: 4 blocks a
+    // compute unit.  More give bands of a few rows, which read half as many rows
+    // again at their edges and never reach the walk of four.  A call, us, with 8192
+    // | 4096 | 2048 | 1024 items: complex64 3000 x 2000 54.8 | 52.4 | 51.6 | 49.3,
+    // 200 x 8000 47.4 | 42.1 | 37.6 | 35.9, 16384 x 8192 515 | 518 | 508 | 499;
+    // complex128 4096^2 98 | 102 | 100 | 102, 16384 x 8192 656 | 655 | 640 | 566
     const long long chunks = (nx + width - 1) / width;
-    long long bands = nblocks / chunks;
+    long long bands = kObservableItems / chunks;
     if (bands < 1) bands = 1;
     if (bands > ny) bands = ny;
     const int band = (int)((ny + bands - 1) / bands);
@@ -466,8 +489,8 @@ hipError_t launch_observables(int dtype, const void* psi, const double* V, int n
                            psi, V, nx, ny, Jx, Jy, eps0, cl, band, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(observables_final, dim3(1), dim3(kReduceThreads), 0, s, partial, nblocks,
-                       result);
+    hipLaunchKernelGGL(observables_final, dim3(1), dim3(kFinalThreads), 0, s,
+                       reinterpret_cast<const double2*>(partial), nblocks, result);
     return hipGetLastError();
 }
 
