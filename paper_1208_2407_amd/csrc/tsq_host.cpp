@@ -1193,8 +1193,7 @@ struct SlabPass {
 // segments (220 tiles on 256 units).
 SlabPass slab_pass(const tsq_plan* p, int stages, int rp, long long cus) {
     SlabPass r{stages, rp, 1};
-    const int strip = tsq::slab_strip(stages), slab = tsq::slab_pairs(stages, rp);
-    const long long columns = (long long)((p->p.nx + strip - 1) / strip) * ((p->p.ny / 2 + slab - 1) / slab);
+    const long long columns = tsq::slab_columns(p->p.nx, p->p.ny, stages, rp).columns;
     const long long pairs = p->p.nz / 2;
     double best = 0.0;
     for (long long segs = 1; segs <= pairs; ++segs) {
@@ -1236,7 +1235,8 @@ int run_slab(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) 
     // One stage below 1.5M sites, where a pass lasts as long as a block's few
     // iterations; two stages above, where it is bound by memory; complex64 with
     // two row pairs per wavefront (a smaller y halo, half the blocks) from 6M.
-    // Steady us per step, complex64 one stage | two, 1 pair | two, 2 pairs:
+    // Steady us per step (with a block for every slab of a left-over strip, see
+    // SlabColumns), complex64 one stage | two, 1 pair | two, 2 pairs:
     // 96^3 7.9 | 8.4 | 11.7, 128 x 160 x 192 24.8 | 21.3 | 23.3, 192^3 37.9 | 35.4 |
     // 31.8, 512^3 769 | 557 | 472; complex128 one | two: 96^3 13.0 | 13.7, 128^3 34.0
     // | 30.4, 512^3 1515 | 1138.

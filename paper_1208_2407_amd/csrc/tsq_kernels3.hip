@@ -136,8 +136,11 @@ static hipError_t launch_slab_with(const void* f, const Pass3Desc& d, bool close
     a.strip_sites = slab_strip(d.stages);
     a.slab_pairs = slab_pairs(d.stages, d.rp);
     a.seg_pairs = d.seg_pairs;
-    a.nstrips = (d.nx + a.strip_sites - 1) / a.strip_sites;
-    a.nslabs = (d.ny / 2 + a.slab_pairs - 1) / a.slab_pairs;
+    const SlabColumns g = slab_columns(d.nx, d.ny, d.stages, d.rp);
+    a.nstrips = g.full_strips;
+    a.nslabs = g.nslabs;
+    a.strip_cols = (int)g.strip_cols;
+    a.pack_lanes = g.pack_lanes;
     a.nsegs = (d.nz / 2 + d.seg_pairs - 1) / d.seg_pairs;
     double Le = 0.0;  // the six even factors
     for (int ax = 0; ax < 3; ++ax) {
@@ -161,7 +164,7 @@ static hipError_t launch_slab_with(const void* f, const Pass3Desc& d, bool close
         return hipLaunchKernel(f, dim3((d.nx / 2 + 255) / 256, (unsigned)std::min(lines, 65535LL)),
                                dim3(256), params, 0, s);
     }
-    const long long tiles = (long long)a.nstrips * a.nslabs * a.nsegs;
+    const long long tiles = g.columns * a.nsegs;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     return hipLaunchKernel(f, dim3((unsigned)tiles), dim3(kWaveSize * kWaves3), params, 0, s);
 }

@@ -448,6 +448,18 @@ __device__ __forceinline__ void slab_stage(SlabPair<typename T::R, RP>& o,
     }
 }
 
+// v modulo n for v up to 2N outside [0, n), n even and at least 2: no division, of
+// which a block of a small mesh, a handful of iterations long, would feel each.
+template <int N>
+__device__ __forceinline__ int wrap_near(int v, int n) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v = v < 0 ? v + n : v;
+        v = v >= n ? v - n : v;
+    }
+    return v;
+}
+
 template <class T, int RP, int NS, bool CLOSE>
 __global__ void __launch_bounds__(kWaveSize * kWaves3)
 slab_kernel(const March3Args<typename T::R> a) {
@@ -464,18 +476,33 @@ slab_kernel(const March3Args<typename T::R> a) {
     const int nb = gridDim.x, full = nb & ~7, b = blockIdx.x;
     const int lb = (b < full) ? ((b & 7) * (full >> 3) + (b >> 3)) : b;
     const int seg = lb % a.nsegs, rest = lb / a.nsegs;
-    const int slab = rest % a.nslabs, strip = rest / a.nslabs;
     const int q0 = seg * a.seg_pairs, q1 = min(q0 + a.seg_pairs, a.nz >> 1);
     const bool rev = (seg & 1) != 0;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const long long plane = (long long)nx * ny;
 
+    // A full strip of one slab, or the strip left over, a slab to each group of
+    // pack_lanes lanes.  A group's outer K lanes are its halo as a wavefront's are, so
+    // what the shifts bring from the next group is never stored; lanes past the last
+    // group count on from it, so that they load what its halo does (below).
+    int strip = rest / a.nslabs, slab = rest % a.nslabs;
+    int glane = lane, glanes = kWaveSize;  // lane of the group, its lanes
+    bool mine = true;
+    if (rest >= a.strip_cols) {
+        const int pack = kWaveSize / a.pack_lanes, sub = min(lane / a.pack_lanes, pack - 1);
+        strip = a.nstrips;
+        slab = (rest - a.strip_cols) * pack + sub;
+        glanes = a.pack_lanes;
+        glane = lane - sub * glanes;
+        mine = slab < a.nslabs;
+    }
+
     // Lanes (row pairs) further past the mesh than the halo of its last column
     // (row pair) load what that halo loads: nothing stored depends on them, and
     // a last strip or slab that is mostly empty costs no memory traffic.
-    const long long xu = (long long)strip * a.strip_sites + (long long)(lane - K) * 2;
-    const int col = wrap(xu < nx - 2 + 2 * K ? xu : (long long)nx - 2 + 2 * K, nx);
-    const bool x_keep = lane >= K && lane < kWaveSize - K && xu < nx;
+    const int xu = strip * a.strip_sites + (glane - K) * 2;
+    const int col = wrap_near<K>(min(xu, nx - 2 + 2 * K), nx);
+    const bool x_keep = mine && glane >= K && glane < glanes - K && xu < nx;
     const int yu = slab * a.slab_pairs + w * RP - K;  // unwrapped first row pair
     // byte offset of each row pair's first row within a plane (psi and the table
     // have the same bytes per site); planes start at wavefront-uniform addresses
@@ -485,7 +512,7 @@ slab_kernel(const March3Args<typename T::R> a) {
     bool keep[RP];
 #pragma unroll
     for (int j = 0; j < RP; ++j) {
-        row[j] = ((unsigned)wrap(2LL * min(yu + j, (ny >> 1) - 1 + K), ny) * (unsigned)nx + (unsigned)col) * E;
+        row[j] = ((unsigned)wrap_near<K>(2 * min(yu + j, (ny >> 1) - 1 + K), ny) * (unsigned)nx + (unsigned)col) * E;
         keep[j] = x_keep && w * RP + j >= K && w * RP + j < kWaves3 * RP - K && 2 * (yu + j) < ny;
     }
     const long long pbytes = plane * E, rbytes = (long long)nx * E;
@@ -493,10 +520,10 @@ slab_kernel(const March3Args<typename T::R> a) {
     const int nit = (q1 - q0) + 2 * K;
     const int tstart = rev ? q1 - 1 + K : q0 - K;
     const int fo = rev ? 1 : 0, zstep = rev ? -2 : 2;
-    int rz = wrap(2LL * tstart, nz);   // first plane of the next pair to load
+    int rz = wrap_near<K>(2 * tstart, nz);   // first plane of the next pair to load
     // ... of the next phase pair: one pair behind where every iteration loads the
     // phases it uses (two stages)
-    int rzp = NS == 1 ? rz : wrap(2LL * tstart - zstep, nz);
+    int rzp = NS == 1 ? rz : wrap_near<K + 1>(2 * tstart - zstep, nz);
     int qout = rev ? q1 - 1 + 2 * K : q0 - 2 * K;
     auto step_z = [&](int& z) {
         z += zstep;
