@@ -150,7 +150,13 @@ int occupancy_cached(int dtype, int steps, bool last, int ppl, bool lds, bool cl
 // one for complex128: more wavefronts hide no more latency there, and every
 // segment reads 2K row pairs of halo (4096^2 complex64 at 2 steps per pass: 65.6
 // us with two blocks a unit, 69.8 with four; 2048^2 complex128 fourth order 54
-// with one, 67 with two).
+// with one, 67 with two).  complex128 passes of one or two steps take all the
+// blocks that fit: their loads are far apart (1000 x 6218, 2 steps: 118 against 136
+// with one a unit; 2048^2 85 against 76).  A mesh of one or two strips fills a
+// quarter or half of a block: as many more blocks count as one (42 x 6218, complex64,
+// 2 steps, 11.4 against 14.4), and three of one strip fit a unit in complex64 where
+// two full ones do (100 x 60000, 20 steps: 224 with three, 311 with two; complex128,
+// whose wavefronts take a whole SIMD's registers each, 273 and 202 at 100 x 20000).
 // A mesh too small for segments of 2K pairs that way: a pass lasts as long as
 // its busiest SIMD, which marches its wavefronts' Q + K pairs (the pipeline's
 // fill skipped) one behind the other, each pair 0.22 us a step alone (complex64)
@@ -168,14 +174,20 @@ int default_seg_rows(const tsq_plan* p, int steps, bool last, int ppl, bool lds,
     const long long pairs = (p->p.ny + 1) / 2, K = steps + (last ? 1 : 0);
     // a launch has one block per segment of kWavesPerBlock strips
     const long long groups = (g.nstrips + tsq::kWavesPerBlock - 1) / tsq::kWavesPerBlock;
-    const long long segs = std::max(1LL, (long long)cus * std::min(occ, c128 ? 1 : 2) / groups);
+    // one or two strips leave most of a block's wavefronts empty: so many more blocks
+    const int fold = std::max(1, tsq::kWavesPerBlock / g.nstrips);
+    const int fits = g.nstrips == 1 && !lds && !c128 ? std::max(occ, 3) : occ;
+    const int full = !c128 ? 2 * fold : steps > 2 ? fold : occ;
+    const long long segs = std::max(1LL, (long long)cus * std::min(fits, full) / groups);
     long long q = (pairs + segs - 1) / segs;
     if (q >= 2 * K) return (int)(2 * q);
     const double share = c128 ? 0.95 : 0.78;
     double best = 0.0;
     for (long long t = 1; t <= 2 * K; ++t) {
-        const long long per_cu = (groups * ((pairs + t - 1) / t) + cus - 1) / cus;
-        const double cost = (double)(t + K) * std::max(1.0, share * (double)per_cu);
+        const long long blocks = groups * ((pairs + t - 1) / t);
+        const long long per_simd = (blocks + (long long)cus * fold - 1) / ((long long)cus * fold);
+        const long long rounds = fold == 1 ? 1 : (blocks + (long long)cus * occ - 1) / ((long long)cus * occ);
+        const double cost = (double)(t + K) * std::max((double)rounds, share * (double)per_simd);
         if (t == 1 || cost < best) {
             best = cost;
             q = t;
