@@ -46,9 +46,6 @@ struct tsq_plan {
     SubStep kind[2];
     tsq_schedule sched;   // resolved (segment_rows may stay 0 = per launch)
     bool sched_default;   // every field was left to the library (small meshes: tile kernels)
-    mutable int64_t tile_steps;     // pick_tile's last answer: for these steps (-1: none) ...
-    mutable bool tile_td;
-    mutable TilePasses tile_passes;
     size_t sites, elem, pelem;
     size_t off_psi2, off_ptab, off_scratch, off_turns, ws_bytes;
     const void* ws_bound;
@@ -334,7 +331,6 @@ TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
     if (cus <= 0) cus = 256;
     // the tallest tiles at the fewest stages: no more blocks per unit than two, or never
     if (tsq::tile_geometry(p->p.nx, p->p.ny, 2, false, 2).tiles > 2LL * cus) return best;
-    if (p->tile_steps == steps && p->tile_td == td) return p->tile_passes;
     const double launch = 2.2;
     const bool closed = p->p.bc == TSQ_BC_CLOSED;
     const double mb = 1e-6 * 3.0 * (double)(p->sites * p->elem);
@@ -368,9 +364,6 @@ TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
             }
         }
     }
-    p->tile_steps = steps;
-    p->tile_td = td;
-    p->tile_passes = best;
     return best;
 }
 
@@ -426,6 +419,7 @@ struct tsq_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int64_t total_tiles = 0;
+    bool coarse = false;  // tile heights by coarse_rows: shorter work lists
 };
 
 namespace {
@@ -497,11 +491,23 @@ long long tile_rows(const tsq_batch* b, const std::vector<tsq::PassDesc>& descs,
     return h;
 }
 
+// Tile height of a batch whose work lists by tile_rows outgrow the buffer they were
+// given: all strips stacked over the resident wavefronts, never under 2K pairs.
+long long coarse_rows(const tsq_batch* b, const std::vector<tsq::PassDesc>& descs, int steps, bool last,
+                      int slots) {
+    long long rows = 0;
+    for (const tsq::PassDesc& d : descs)
+        rows += (long long)tsq::march_geometry(d.nx, d.ny, steps, last, b->sched.pairs_per_lane, 2).nstrips * d.ny;
+    const long long h = std::max<long long>((rows + slots - 1) / slots, 4LL * (steps + (last ? 1 : 0)));
+    return (h + 1) & ~1LL;
+}
+
 template <class R>
 void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::PassDesc>& descs,
                    int cus, int slots) {
     const int ppl = b->sched.pairs_per_lane;
     const long long h = b->sched.segment_rows > 0 ? b->sched.segment_rows
+                        : b->coarse               ? coarse_rows(b, descs, steps, last, slots)
                                                   : tile_rows(b, descs, steps, last, cus, slots);
     std::vector<tsq::BatchJob<R>> jobs;
     std::vector<tsq::BatchTile> tiles;
@@ -573,8 +579,8 @@ void drop_graph(tsq_batch* b) {
 
 extern "C" {
 
-int tsq_batch_create(tsq_plan* const* plans, void* const* psi, void* const* ws, const int64_t* steps,
-                     int32_t n, const tsq_schedule* schedule, tsq_batch** out) {
+static int create_batch(tsq_plan* const* plans, void* const* psi, void* const* ws, const int64_t* steps,
+                        int32_t n, const tsq_schedule* schedule, bool coarse, tsq_batch** out) {
     if (!plans || !psi || !ws || !steps || !out || n < 1)
         return fail(TSQ_ERR_ARG, "null argument or empty batch");
     const int dtype = plans[0] ? plans[0]->p.dtype : -1;
@@ -609,6 +615,7 @@ int tsq_batch_create(tsq_plan* const* plans, void* const* psi, void* const* ws, 
     if (!b) return fail(TSQ_ERR_ARG, "out of host memory");
     b->dtype = dtype;
     b->sched = sc;
+    b->coarse = coarse;
     for (int i = 0; i < n; ++i) {
         std::vector<Run> runs;
         const bool cb = steps[i] > 0 && pass_runs(steps[i], sc.steps_per_pass, runs);
@@ -665,6 +672,11 @@ int tsq_batch_create(tsq_plan* const* plans, void* const* psi, void* const* ws, 
     }
     *out = b;
     return ok();
+}
+
+int tsq_batch_create(tsq_plan* const* plans, void* const* psi, void* const* ws, const int64_t* steps,
+                     int32_t n, const tsq_schedule* schedule, tsq_batch** out) {
+    return create_batch(plans, psi, ws, steps, n, schedule, false, out);
 }
 
 int tsq_batch_destroy(tsq_batch* b) {
@@ -771,9 +783,18 @@ int tsq::batch_evolve_into(tsq_plan* const* plans, void* const* psi, void* const
                            const int64_t* steps, int32_t n, const tsq_schedule* schedule,
                            void* bws, size_t bws_bytes, void* stream, size_t* need) {
     tsq_batch* b = nullptr;
-    int rc = tsq_batch_create(plans, psi, ws, steps, n, schedule, &b);
+    int rc = create_batch(plans, psi, ws, steps, n, schedule, false, &b);
     if (rc) return rc;
-    if (need) tsq_batch_workspace_size(b, need);
+    size_t bytes = 0;
+    tsq_batch_workspace_size(b, &bytes);
+    if (bytes > bws_bytes && !b->sched.segment_rows) {
+        tsq_batch_destroy(b);
+        b = nullptr;
+        rc = create_batch(plans, psi, ws, steps, n, schedule, true, &b);
+        if (rc) return rc;
+        tsq_batch_workspace_size(b, &bytes);
+    }
+    if (need) *need = bytes;
     rc = tsq_batch_upload(b, bws, bws_bytes, stream);
     if (!rc) rc = tsq_batch_launch(b, 0, stream);
     // the upload reads pageable host memory, which the copy has staged by the
@@ -885,7 +906,6 @@ int tsq_plan_create(const tsq_problem* pr, tsq_plan** out) {
               (long long)pr->nx * pr->ny * (pr->dtype == TSQ_C128 ? 16 : 8) <= tsq::kMaxSlabPlane;
     resolve_schedule(tsq_schedule{0, 0, 0, 0}, p->sched);
     p->sched_default = true;
-    p->tile_steps = -1;
     p->sites = (size_t)pr->nx * (size_t)pr->ny * (size_t)p->p.nz;
     p->elem = pr->dtype == TSQ_C128 ? 16 : 8;
     // bytes per site of a phase-table area: complex128 exp(-i phi) (16);
@@ -942,7 +962,6 @@ int tsq_plan_set_schedule(tsq_plan* plan, const tsq_schedule* sc) {
     if (plan->p.bc == TSQ_BC_CLOSED && r.pairs_per_lane != 1)
         return fail(TSQ_ERR_ARG, "closed meshes run with 1 pair per lane");
     plan->sched = r;
-    plan->tile_steps = -1;
     plan->sched_default = !sc->steps_per_pass && !sc->segment_rows && !sc->pairs_per_lane &&
                           !sc->phase_store;
     return ok();
