@@ -369,7 +369,7 @@ observables_pairs(const void* __restrict__ psi, const double* __restrict__ V, in
 // bounds it (256 threads with one load in flight took 8.9 us for 8192 partial
 // sums; a call at 3000 x 2000, complex64, 59.4 then and 54.8 with this).
 constexpr int kFinalThreads = 1024;
-constexpr int kObservableItems = 1024;  // work items of a 2D mesh's sums (launch_observables)
+constexpr long long kObservableItems = 1024;  // least work items of a large 2D mesh's sums
 __global__ void __launch_bounds__(kFinalThreads)
 observables_final(const double2* __restrict__ partial, int nblocks, double* __restrict__ result) {
     __shared__ double sn[kFinalThreads / kWaveSize], se[kFinalThreads / kWaveSize];
@@ -467,9 +467,12 @@ hipError_t launch_observables(int dtype, const void* psi, const double* V, int n
     // again at their edges and never reach the walk of four.  A call, us, with 8192
     // | 4096 | 2048 | 1024 items: complex64 3000 x 2000 54.8 | 52.4 | 51.6 | 49.3,
     // 200 x 8000 47.4 | 42.1 | 37.6 | 35.9, 16384 x 8192 515 | 518 | 508 | 499;
-    // complex128 4096^2 98 | 102 | 100 | 102, 16384 x 8192 656 | 655 | 640 | 566
+    // complex128 4096^2 98 | 102 | 100 | 102, 16384 x 8192 656 | 655 | 640 | 566.  Bands
+    // of more than 256 rows only past `nblocks` items: 32768^2 complex64 takes 3.4 ms
+    // at 256 rows (8192 items) and 4.15 at 2048, whose blocks are far apart in memory.
     const long long chunks = (nx + width - 1) / width;
-    long long bands = kObservableItems / chunks;
+    long long bands = std::max(kObservableItems / chunks,
+                               std::min(nblocks / chunks, (long long)(ny + 255) / 256));
     if (bands < 1) bands = 1;
     if (bands > ny) bands = ny;
     const int band = (int)((ny + bands - 1) / bands);
