@@ -475,7 +475,13 @@ slab_kernel(const March3Args<typename T::R> a) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const int nb = gridDim.x, full = nb & ~7, b = blockIdx.x;
     const int lb = (b < full) ? ((b & 7) * (full >> 3) + (b >> 3)) : b;
-    const int seg = lb % a.nsegs, rest = lb / a.nsegs;
+    // XCD-aware: an XCD takes a run of neighbouring slabs of one segment, which read
+    // each other's y halo (a third to all of what they keep) through one L2.  With a
+    // column's segments next to each other instead, which share the smaller z halo, us
+    // per step: complex64 512^3 421 (405 this way), 192^3 32.4 (28.8), complex128
+    // 512^3 1149 (1046), 106^3 17.3 (15.5); 100 x 200 x 60, segments of two pairs,
+    // 8.7 (9.3) and 15.7 (16.4).
+    const int cols = gridDim.x / a.nsegs, seg = lb / cols, rest = lb % cols;
     const int q0 = seg * a.seg_pairs, q1 = min(q0 + a.seg_pairs, a.nz >> 1);
     const bool rev = (seg & 1) != 0;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
