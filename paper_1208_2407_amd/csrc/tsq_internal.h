@@ -288,6 +288,12 @@ int march_blocks_per_cu(int dtype, int steps, bool last, int pairs_per_lane, boo
 bool march_variant_exists(int dtype, int steps, bool last, int pairs_per_lane, bool phase_lds,
                           bool closed = false, bool td = false);
 
+// Whether a static periodic second-order pass keeps 64-bit addresses per lane: the
+// complex64 march of one mesh addresses rows by the scalar unit and a lane's site by a
+// 32-bit byte offset within its row, so rows of more than 4 GiB (only 2 x more than 2^29
+// sites are that long) run the instances without it (Variant::Lanes; the same bits).
+bool lane_addresses(int dtype, int nx);
+
 // All launchers return hipSuccess or the launch error.
 // exp(-i dt (V + eps0) / hbar) times `scale` per site.
 // Per-site scale of the phase table: g, or on a closed mesh gx on the last

@@ -674,7 +674,8 @@ template <class T, bool TD>
 using TableT = std::conditional_t<TD, double2, typename T::TT>;
 
 // UA (complex64, one problem, static, second order): rows are addressed by
-// the scalar unit, see load_pair.  At 32768^2 the 6-step pass, bound by its
+// the scalar unit, see load_pair; a lane's offset within its row has 32 bits
+// (lane_addresses names the rows that are too long).  At 32768^2 the 6-step pass, bound by its
 // vector instructions, takes 5.6% less time; the marches bound by memory and the
 // batched one, whose row addresses come from a job record, run 1 to 2% slower
 // that way and keep per-lane addresses.
@@ -980,7 +981,8 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
 }
 
 // One problem, one tile per wavefront.
-template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4 = false>
+template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4 = false,
+          bool UA = sizeof(typename T::R) == 4 && !CLOSED && !TD && !U4>
 __global__ void __launch_bounds__(kWaveSize * kWavesPerBlock)
 march_kernel(const MarchArgs<typename T::R> a) {
     __shared__ WaveRing<PhaseT<T, TD>, S, PPL, LDS> rings[LDS ? kWavesPerBlock : 1];
@@ -1015,7 +1017,6 @@ march_kernel(const MarchArgs<typename T::R> a) {
     const int grp = lb - seg * ngroups;
     const int strip = grp * kWavesPerBlock + wave;
     if (strip >= a.nstrips) return;  // uniform per wavefront
-    constexpr bool UA = sizeof(typename T::R) == 4 && !CLOSED && !TD && !U4;
     march_tile<T, S, LAST, PPL, LDS, CLOSED, TD, U4, UA>(a, strip, seg, seg & 1, lane,
                                                  &rings[LDS ? wave : 0].v[0][0][0][lane], turns);
 }
@@ -1052,8 +1053,9 @@ march_batch_kernel(const BatchJob<typename T::R>* __restrict__ jobs,
 // 1..kMaxSteps (1 pair per lane), single and batched; closed meshes: both
 // rings with 1 pair per lane, single only; time-dependent potentials
 // (periodic or closed): both rings, 1 pair per lane, at most kMaxTdSteps
-// steps per pass, single only.
-enum class Variant { Single, Batch, Closed, TimeDep, ClosedTimeDep, Order4 };
+// steps per pass, single only; complex64 with lane addresses (see
+// lane_addresses): 1 pair per lane, LDS ring beyond kMaxRegSteps only.
+enum class Variant { Single, Batch, Closed, TimeDep, ClosedTimeDep, Order4, Lanes };
 
 template <class T, int S, bool LAST, int PPL, bool LDS, Variant V>
 const void* kernel_ptr() {
@@ -1068,7 +1070,12 @@ const void* kernel_ptr() {
         return reinterpret_cast<const void*>(&march_batch_kernel<T, S, LAST, PPL, LDS>);
     else if constexpr (PPL != 1)
         return nullptr;
-    else if constexpr (V == Variant::Closed)
+    else if constexpr (V == Variant::Lanes) {
+        if constexpr (LDS == (S > kMaxRegSteps))
+            return reinterpret_cast<const void*>(&march_kernel<T, S, LAST, 1, LDS, false, false, false, false>);
+        else
+            return nullptr;
+    } else if constexpr (V == Variant::Closed)
         return reinterpret_cast<const void*>(&march_kernel<T, S, LAST, PPL, LDS, true, false>);
     else if constexpr (V == Variant::TimeDep)
         return reinterpret_cast<const void*>(&march_kernel<T, S, LAST, PPL, LDS, false, true>);
