@@ -206,27 +206,11 @@ struct C64 {
 // hi float (bits 8 and up, 23 of them with the sign apart) and a lo float (the
 // low byte, which one conversion extracts), the pair the complex64 phase
 // multiply takes.
-__device__ __forceinline__ float4 split_phase(int2 t) {
-    return make_float4((float)(t.x & ~0xff), (float)(t.y & ~0xff), (float)(unsigned char)t.x,
-                       (float)(unsigned char)t.y);
-}
 __device__ __forceinline__ double2 decode_phase(double2 t) { return t; }
 __device__ __forceinline__ float4 decode_phase(int2 t) {
     const float sc = 0x1p-30f;
-    const float4 p = split_phase(t);
-    return make_float4(p.x * sc, p.y * sc, p.z * sc, p.w * sc);
-}
-
-// The phase multiply by a table entry as stored.  complex64: the scale 2^-30
-// comes last (two multiplies instead of four; a power of two, so the same bits
-// as apply_phase of the decoded entry unless a part of psi is beyond 1e29).
-__device__ __forceinline__ void apply_table(double& re, double& im, const double2 p) {
-    apply_phase(re, im, p);
-}
-__device__ __forceinline__ void apply_table(float& re, float& im, const int2 t) {
-    apply_phase(re, im, split_phase(t));
-    re *= 0x1p-30f;
-    im *= 0x1p-30f;
+    return make_float4((float)(t.x & ~0xff) * sc, (float)(t.y & ~0xff) * sc,
+                       (float)(unsigned char)t.x * sc, (float)(unsigned char)t.y * sc);
 }
 
 template <class R, int SPL>

@@ -432,8 +432,10 @@ __device__ __forceinline__ void slab_stage(SlabPair<typename T::R, RP>& o,
                 take(i, tf, tg);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    apply_table(o.f[i].re[c], o.f[i].im[c], tf[c]);
-                    apply_table(o.g[i].re[c], o.g[i].im[c], tg[c]);
+                    // the entry is scaled before the product: as it is stored
+                    // (2^30), parts of psi beyond 1e29 would overflow
+                    apply_phase(o.f[i].re[c], o.f[i].im[c], decode_phase(tf[c]));
+                    apply_phase(o.g[i].re[c], o.g[i].im[c], decode_phase(tg[c]));
                 }
                 pair_y_t(o.f[i], o.g[i], ez);
             }
