@@ -1033,6 +1033,7 @@ int tsq_set_potential(tsq_plan* plan, const double* V, void* ws, size_t ws_bytes
             scale.wy0 = (plan->p.ny & 1) ? (long long)(plan->p.ny - 1) * plan->p.nx : -1;
         } else {
             scale.g = std::exp(-0.5 * table_log(plan, k));
+            if (plan->three_d && plan->slab3) scale.unit = tsq::slab_table_unit(table_log(plan, k));
         }
         hipError_t e = tsq::launch_phase_table(plan->p.dtype, V, w + u.off_ptab,
                                                (long long)plan->sites, u.dt, plan->eps0,

@@ -23,6 +23,7 @@ struct March3Args {
     // Slab march (tangent form, see MarchArgs): odd factors opening the
     // pass (x: s', d' of the delta form), tangents at dt and dt/2, closing odd x.
     R o1x[2], o1t[3], t2[3], t1[3], c1x[2];
+    R table_unit;  // slab march, complex64: 1 per fixed-point unit of a table entry
 };
 
 constexpr int kWaves3 = 8;  // wavefronts per block of the 3D march (one row pair each)
@@ -79,6 +80,16 @@ double step3_log_sec2(const Coef64* oh, const Coef64* o2) {
     for (int ax = 0; ax < 3; ++ax)
         L += log_sec2(tangent<R>(o2[ax])) + 2.0 * log_sec2(tangent<R>(oh[ax]));
     return L;
+}
+// Fixed-point units per 1 of a complex64 table whose entries have the modulus
+// g = exp(-L/2): the power of two that takes g to [2^30, 2^31), so an entry keeps 2^-31
+// of itself at any angle, as one of modulus 1 does at 2^30 (at 2^30 for all, entries
+// lose up to 3.8 bits near 1 rad a step, the same at every step).
+inline double slab_table_unit(double L) {
+    const double g = std::exp(-0.5 * L);
+    int e = 30 - std::ilogb(g);
+    if (std::ldexp(g, e) > 2147483647.0) --e;
+    return std::ldexp(1.0, e);
 }
 hipError_t launch_pass3(int dtype, const Pass3Desc& d, hipStream_t s);
 hipError_t launch_observables3(int dtype, const void* psi, const double* V, int nx, int ny, int nz,

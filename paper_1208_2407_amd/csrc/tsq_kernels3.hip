@@ -158,6 +158,7 @@ static hipError_t launch_slab_with(const void* f, const Pass3Desc& d, bool close
                        Le + log_sec2(a.o1t[1]) + log_sec2(a.o1t[2]) - step3_log_sec2<R>(d.oh, d.o2),
                        a.o1x[0], a.o1x[1]);
     delta_odd_x<R>(d.oh[0].al, log_sec2(a.t1[1]) + log_sec2(a.t1[2]), a.c1x[0], a.c1x[1]);
+    a.table_unit = (R)(1.0 / slab_table_unit(step3_log_sec2<R>(d.oh, d.o2)));
     void* params[] = {&a};
     if (close_only) {
         const long long lines = (long long)(d.ny / 2) * (d.nz / 2);

@@ -206,9 +206,8 @@ struct C64 {
 // hi float (bits 8 and up, 23 of them with the sign apart) and a lo float (the
 // low byte, which one conversion extracts), the pair the complex64 phase
 // multiply takes.
-__device__ __forceinline__ double2 decode_phase(double2 t) { return t; }
-__device__ __forceinline__ float4 decode_phase(int2 t) {
-    const float sc = 0x1p-30f;
+__device__ __forceinline__ double2 decode_phase(double2 t, double = 1.0) { return t; }
+__device__ __forceinline__ float4 decode_phase(int2 t, float sc = 0x1p-30f) {
     return make_float4((float)(t.x & ~0xff) * sc, (float)(t.y & ~0xff) * sc,
                        (float)(unsigned char)t.x * sc, (float)(unsigned char)t.y * sc);
 }

@@ -433,9 +433,9 @@ __device__ __forceinline__ void slab_stage(SlabPair<typename T::R, RP>& o,
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     // the entry is scaled before the product: as it is stored
-                    // (2^30), parts of psi beyond 1e29 would overflow
-                    apply_phase(o.f[i].re[c], o.f[i].im[c], decode_phase(tf[c]));
-                    apply_phase(o.g[i].re[c], o.g[i].im[c], decode_phase(tg[c]));
+                    // (2^30 and more), parts of psi beyond 1e29 would overflow
+                    apply_phase(o.f[i].re[c], o.f[i].im[c], decode_phase(tf[c], a.table_unit));
+                    apply_phase(o.g[i].re[c], o.g[i].im[c], decode_phase(tg[c], a.table_unit));
                 }
                 pair_y_t(o.f[i], o.g[i], ez);
             }

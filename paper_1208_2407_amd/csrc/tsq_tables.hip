@@ -105,13 +105,14 @@ __global__ void phase_table_c128(const double* __restrict__ V, double2* __restri
     });
 }
 
-// complex64: cos(phi) and -sin(phi) as 32-bit fixed point, value * 2^30
-// rounded to nearest (|value| <= 1, so 2^30 fits; error <= 2^-31 per part).
+// complex64: cos(phi) and -sin(phi) as 32-bit fixed point, value * sc.unit
+// rounded to nearest (2^30 on 2D meshes: |value| <= 1, so it fits; error <= 2^-31
+// per part; 3D meshes of the slab march: see slab_table_unit).
 __global__ void phase_table_c64(const double* __restrict__ V, int2* __restrict__ P,
                                 long long n, double dt, double eps0, double hbar, TableScale sc) {
     phase_sites<true>(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
         const double g = site_scale(sc, l);
-        P[l] = make_int2(__double2int_rn(g * c * 0x1p30), __double2int_rn(-(g * s) * 0x1p30));
+        P[l] = make_int2(__double2int_rn(g * c * sc.unit), __double2int_rn(-(g * s) * sc.unit));
     });
 }
 
