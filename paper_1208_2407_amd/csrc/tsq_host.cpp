@@ -1033,7 +1033,15 @@ int tsq_set_potential(tsq_plan* plan, const double* V, void* ws, size_t ws_bytes
             scale.wy0 = (plan->p.ny & 1) ? (long long)(plan->p.ny - 1) * plan->p.nx : -1;
         } else {
             scale.g = std::exp(-0.5 * table_log(plan, k));
-            if (plan->three_d && plan->slab3) scale.unit = tsq::slab_table_unit(table_log(plan, k));
+            if (plan->three_d && plan->slab3) {
+                const tsq::Coef64 oh[3] = {plan->oxh, plan->oyh, plan->ozh};
+                const tsq::Coef64 o2[3] = {plan->ox2, plan->oy2, plan->oz2};
+                scale.unit = tsq::slab_table_unit(table_log(plan, k));
+                if (plan->p.dtype == TSQ_C128)
+                    tsq::slab_table_scale<double>(oh, o2, scale);
+                else
+                    tsq::slab_table_scale<float>(oh, o2, scale);
+            }
         }
         hipError_t e = tsq::launch_phase_table(plan->p.dtype, V, w + u.off_ptab,
                                                (long long)plan->sites, u.dt, plan->eps0,

@@ -299,9 +299,10 @@ bool lane_addresses(int dtype, int nx);
 // Per-site scale of the phase table: g, or on a closed mesh gx on the last
 // column (column wx >= 0: an odd width leaves it without an even x partner),
 // gy on the last row (from site wy0 >= 0: an odd height), gxy on both.
+// g_lo: the rest of g that its double does not hold (complex128, meshes without walls).
 // unit: fixed-point units per 1 of a complex64 entry.
 struct TableScale {
-    double g = 1.0, gx = 1.0, gy = 1.0, gxy = 1.0;
+    double g = 1.0, gx = 1.0, gy = 1.0, gxy = 1.0, g_lo = 0.0;
     long long nx = 1, wx = -1, wy0 = -1;
     double unit = 0x1p30;
 };

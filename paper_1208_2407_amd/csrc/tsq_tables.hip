@@ -101,7 +101,7 @@ __global__ void phase_table_c128(const double* __restrict__ V, double2* __restri
                                  long long n, double dt, double eps0, double hbar, TableScale sc) {
     phase_sites<false>(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
         const double g = site_scale(sc, l);
-        P[l] = make_double2(g * c, -(g * s));
+        P[l] = make_double2(__builtin_fma(g, c, sc.g_lo * c), -__builtin_fma(g, s, sc.g_lo * s));
     });
 }
 
