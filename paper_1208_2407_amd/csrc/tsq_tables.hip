@@ -71,20 +71,67 @@ __device__ __forceinline__ void sincos_table(double x, double* s, double* c) {
     *c = ((q + 1) & 2) ? -cv : cv;
 }
 
-template <bool TABLE, class Store>
+// g cos x and g sin x, g = (g, g_lo) in two parts, each with one rounding: formed from
+// a rounded cosine an entry would round twice, and its error repeats at every step
+// (200 steps of 0.01 rad a step and axis on a random 3D state: 5.7e-15, this way 4.3e-15).
+// The reduction of sincos_table with what it rounds off kept in r_lo (the angle's third
+// part of pi/2 is below 1e-23), cos = 1 - r^2/2 and sin = r - r^3/6 with the rest of the
+// series in a tail that is small beside them, and the products by g with their FMA
+// remainders.
+__device__ __forceinline__ void scaled_sincos(double x, double g, double g_lo, double* gs, double* gc) {
+    if (!(fabs(x) < 0x1p30)) {
+        double s, c;
+        sincos(x, &s, &c);
+        *gs = __builtin_fma(g, s, g_lo * s);
+        *gc = __builtin_fma(g, c, g_lo * c);
+        return;
+    }
+    const double shifter = 0x1.8p52;
+    const double t = __builtin_fma(x, 0x1.45f306dc9c883p-1, shifter);  // 2/pi
+    const double j = t - shifter;
+    const int q = __double2loint(t);
+    const double r0 = __builtin_fma(-j, 0x1.921fb54442d18p+0, x);  // exact
+    const double low = j * 0x1.1a62633145c07p-54;
+    const double r = r0 - low, b = r - r0;
+    const double r_lo = (r0 - (r - b)) - (low + b);
+    const double z = r * r, z_lo = __builtin_fma(r, r, -z);
+    double a = 1.0 / 355687428096000.0;  // sin r = r - r^3/6 + r^3 z a, through r^17 (omitted: 8e-20)
+    a = __builtin_fma(a, z, -1.0 / 1307674368000.0);
+    a = __builtin_fma(a, z, 1.0 / 6227020800.0);
+    a = __builtin_fma(a, z, -1.0 / 39916800.0);
+    a = __builtin_fma(a, z, 1.0 / 362880.0);
+    a = __builtin_fma(a, z, -1.0 / 5040.0);
+    a = __builtin_fma(a, z, 1.0 / 120.0);
+    double d = -1.0 / 6402373705728000.0;  // cos r = 1 - z/2 + z^2 d, through r^18 (3e-21)
+    d = __builtin_fma(d, z, 1.0 / 20922789888000.0);
+    d = __builtin_fma(d, z, -1.0 / 87178291200.0);
+    d = __builtin_fma(d, z, 1.0 / 479001600.0);
+    d = __builtin_fma(d, z, -1.0 / 3628800.0);
+    d = __builtin_fma(d, z, 1.0 / 40320.0);
+    d = __builtin_fma(d, z, -1.0 / 720.0);
+    d = __builtin_fma(d, z, 1.0 / 24.0);
+    const double h = 0.5 * z, w = 1.0 - h;
+    const double c_tail = __builtin_fma(z * z, d, ((1.0 - w) - h) - 0.5 * z_lo - r * r_lo);
+    const double c6 = -1.0 / 6.0, c6_lo = -9.2518585385429707656e-18;
+    const double r3 = r * z, r3_lo = __builtin_fma(r, z, -r3) + r * z_lo;
+    const double u = c6 * r3, u_lo = __builtin_fma(c6, r3, -u) + (c6 * r3_lo + c6_lo * r3);
+    const double v = r + u;
+    const double s_tail = __builtin_fma(r3 * z, a, ((r - v) + u) + u_lo + r_lo * w);
+    const double pc = g * w, ps = g * v;
+    const double cs = pc + (__builtin_fma(g, w, -pc) + __builtin_fma(g, c_tail, g_lo * w));
+    const double sn = ps + (__builtin_fma(g, v, -ps) + __builtin_fma(g, s_tail, g_lo * v));
+    const double sv = (q & 1) ? cs : sn, cv = (q & 1) ? sn : cs;
+    *gs = (q & 2) ? -sv : sv;
+    *gc = ((q + 1) & 2) ? -cv : cv;
+}
+
+// `store(site, angle)` for every site of the thread.
+template <class Store>
 __device__ __forceinline__ void phase_sites(const double* __restrict__ V, long long n, double dt,
                                             double eps0, double hbar, Store&& store) {
     const long long stride = (long long)gridDim.x * blockDim.x;
     long long l = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    auto phase = [&](double v, long long at) {
-        double s, c;
-        const double x = dt * (v + eps0) / hbar;
-        if constexpr (TABLE)
-            sincos_table(x, &s, &c);
-        else
-            sincos(x, &s, &c);
-        store(at, c, s);
-    };
+    auto phase = [&](double v, long long at) { store(at, dt * (v + eps0) / hbar); };
     for (; l + 3 * stride < n; l += 4 * stride) {
         double v[4];
 #pragma unroll
@@ -99,9 +146,21 @@ __device__ __forceinline__ void phase_sites(const double* __restrict__ V, long l
 
 __global__ void phase_table_c128(const double* __restrict__ V, double2* __restrict__ P,
                                  long long n, double dt, double eps0, double hbar, TableScale sc) {
-    phase_sites<false>(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
+    phase_sites(V, n, dt, eps0, hbar, [&](long long l, double x) {
+        double s, c;
+        sincos(x, &s, &c);
         const double g = site_scale(sc, l);
-        P[l] = make_double2(__builtin_fma(g, c, sc.g_lo * c), -__builtin_fma(g, s, sc.g_lo * s));
+        P[l] = make_double2(g * c, -(g * s));
+    });
+}
+
+// Meshes whose scale has two parts (3D).
+__global__ void phase_table_c128_two(const double* __restrict__ V, double2* __restrict__ P,
+                                     long long n, double dt, double eps0, double hbar, TableScale sc) {
+    phase_sites(V, n, dt, eps0, hbar, [&](long long l, double x) {
+        double s, c;
+        scaled_sincos(x, sc.g, sc.g_lo, &s, &c);
+        P[l] = make_double2(c, -s);
     });
 }
 
@@ -110,7 +169,9 @@ __global__ void phase_table_c128(const double* __restrict__ V, double2* __restri
 // per part; 3D meshes of the slab march: see slab_table_unit).
 __global__ void phase_table_c64(const double* __restrict__ V, int2* __restrict__ P,
                                 long long n, double dt, double eps0, double hbar, TableScale sc) {
-    phase_sites<true>(V, n, dt, eps0, hbar, [&](long long l, double c, double s) {
+    phase_sites(V, n, dt, eps0, hbar, [&](long long l, double x) {
+        double s, c;
+        sincos_table(x, &s, &c);
         const double g = site_scale(sc, l);
         P[l] = make_int2(__double2int_rn(g * c * sc.unit), __double2int_rn(-(g * s) * sc.unit));
     });
@@ -453,7 +514,10 @@ hipError_t launch_phase_table(int dtype, const double* V, void* ptab, long long 
     long long want = (sites + threads - 1) / threads;
     want = want <= round ? want : std::max(round, (want + 3) / 4);
     const int blocks = (int)(want < 8192 ? want : 8192);
-    if (dtype == 1)
+    if (dtype == 1 && scale.g_lo != 0.0)
+        hipLaunchKernelGGL(phase_table_c128_two, dim3(blocks), dim3(threads), 0, s, V,
+                           reinterpret_cast<double2*>(ptab), sites, dt, eps0, hbar, scale);
+    else if (dtype == 1)
         hipLaunchKernelGGL(phase_table_c128, dim3(blocks), dim3(threads), 0, s, V,
                            reinterpret_cast<double2*>(ptab), sites, dt, eps0, hbar, scale);
     else
