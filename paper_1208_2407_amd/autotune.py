@@ -8,6 +8,10 @@ under each candidate (HIP events on the current stream), keeps the fastest
 per pass: it computes fewer redundant halo sites for the same speed), and
 caches the choice per (device architecture, dtype, mesh) in a JSON file
 (``$TSQ_AUTOTUNE_CACHE``, default ``~/.cache/tsq/autotune.json``).
+
+With every field 0 the library chooses, and runs small 2D meshes in its tile
+kernels, whose passes no explicit schedule makes; so leaving the choice to the
+library is timed too.
 """
 from __future__ import annotations
 
@@ -32,6 +36,11 @@ DEFAULT_CANDIDATES: List[Schedule] = (
 
 # relative time difference below which two schedules count as equally fast
 TIE = 0.02
+
+
+# every field left to the library, and what tsq_plan_get_schedule reports then
+LIBRARY: Schedule = (0, 0, 0, 0)
+LIBRARY_REPORTS: Schedule = (5, 0, 1, 1)
 
 
 def cache_path() -> str:
@@ -112,7 +121,8 @@ def tune(plan, psi, *, candidates: Optional[Iterable[Schedule]] = None, steps: i
     Two stages: steps per pass and phase store at the one-round segment height
     (segment_rows 0), then the segment height (SEGMENT_ROWS, tile shape along y)
     for the winner, which keeps 0 unless another height is faster beyond `TIE`.
-    `psi` is not modified (a scratch copy is evolved).  Returns the schedule and
+    2D meshes keep the library's own choice, (0, 0, 0, 0), where it is faster than
+    that beyond `TIE` (the tile kernels).  `psi` is not modified (a scratch copy is evolved).  Returns the schedule and
     the timing table {"S,seg,ppl,store": ms}."""
     import torch
     arch = torch.cuda.get_device_properties(psi.device).gcnArchName.split(":")[0]
@@ -139,19 +149,7 @@ def tune(plan, psi, *, candidates: Optional[Iterable[Schedule]] = None, steps: i
     for cand in (candidates or DEFAULT_CANDIDATES):
         run(cand)
     best = pick(timed)
-    # small meshes: with every field 0 the library may take its tile kernels, whose
-    # passes no explicit schedule makes
-    own = False
-    if candidates is None and plan.problem.nz < 2:
-        plan.set_schedule(0, 0, 0, 0)
-        passes = plan.passes(steps)
-        plan.set_schedule(*plan.schedule())
-        if passes != plan.passes(steps):
-            run((0, 0, 0, 0))
-            own = min(timed)[1] == (0, 0, 0, 0)
-    if own:
-        best = (0, 0, 0, 0)
-    elif segments and candidates is None:
+    if segments and candidates is None:
         base = next(ms for ms, c in timed if c == best)
         seg_timed = [(base, best)]
         for rows in SEGMENT_ROWS:
@@ -163,6 +161,10 @@ def tune(plan, psi, *, candidates: Optional[Iterable[Schedule]] = None, steps: i
         fastest = min(seg_timed)
         if fastest[0] < base * (1.0 - TIE):
             best = fastest[1]
+    if candidates is None and plan.problem.nz < 2:
+        explicit = next(ms for ms, c in timed if c == best)
+        if run(LIBRARY) < explicit * (1.0 - TIE):
+            best = LIBRARY
     del scratch
     plan.set_schedule(*best)
     if use_cache:
@@ -181,7 +183,7 @@ def time_schedule_td(plan, psi, f, schedule: Schedule, repeats: int = 2) -> floa
     """Best-of-`repeats` milliseconds of plan.evolve_td(psi, f) under `schedule`."""
     import torch
     plan.set_schedule(*schedule)
-    plan.evolve_td(psi, f[: 2 * schedule[0]])  # warm the code path
+    plan.evolve_td(psi, f[: 2 * (schedule[0] or 5)])  # warm the code path
     best = float("inf")
     for _ in range(repeats):
         e0 = torch.cuda.Event(enable_timing=True)
@@ -199,30 +201,37 @@ def tune_td(plan, psi, f, *, candidates: Optional[Iterable[Schedule]] = None, st
     """Pick the fastest schedule for a plan holding a time-dependent table
     (tsq_set_potential_td) and set it: times `steps` steps of the modulation `f`
     (repeated if shorter) on a scratch copy of `psi` under each candidate; cached
-    per device, dtype, mesh, boundary and library, apart from the static choice."""
+    per device, dtype, mesh, boundary and library, apart from the static choice.
+    Among the default candidates LIBRARY_REPORTS stands for every field left to the
+    library (tile kernels on small meshes, else that schedule): it is timed and set
+    on the plan that way, and reported by its name."""
     import numpy as np
     import torch
     arch = torch.cuda.get_device_properties(psi.device).gcnArchName.split(":")[0]
     key = _key(arch, plan.dtype, plan.problem.nx, plan.problem.ny, plan.problem.order,
                plan.problem.bc) + "|td"
     db = _load() if use_cache else {}
+
+    def fields(cand):
+        return LIBRARY if candidates is None and tuple(cand) == LIBRARY_REPORTS else cand
+
     if use_cache and key in db and len(db[key].get("schedule", [])) == 4:
         sched = tuple(db[key]["schedule"])
-        plan.set_schedule(*sched)
+        plan.set_schedule(*fields(sched))
         return sched, db[key].get("table", {})
     fs = np.resize(np.asarray(f, dtype=np.float64), steps)
     scratch = psi.clone()
     table: Dict[str, float] = {}
     timed: List[Tuple[float, Schedule]] = []
     for cand in (candidates or TD_CANDIDATES):
-        ms = time_schedule_td(plan, scratch, fs, cand)
+        ms = time_schedule_td(plan, scratch, fs, fields(cand))
         table[",".join(map(str, cand))] = ms
         timed.append((ms, tuple(cand)))
         if log:
             log(f"autotune {key} S={cand[0]} store={cand[3]}: {ms:.3f} ms")
     best = pick(timed)
     del scratch
-    plan.set_schedule(*best)
+    plan.set_schedule(*fields(best))
     if use_cache:
         db[key] = {"schedule": list(best), "table": table, "steps": steps}
         _store(db)
