@@ -310,8 +310,11 @@ int tsq_batch_evolve(tsq_plan* const* plans, void* const* psi_dev, void* const* 
  * (16 MiB per GPU, kept until the process ends) instead of a caller buffer.
  * Allocates nothing.  Calls on one GPU share that array: calls that overlap
  * on one GPU (different streams, or host threads) race; calls in one stream
- * are ordered.  Errors: those of tsq_batch_evolve; TSQ_ERR_WORKSPACE when the
- * work lists (tsq_batch_evolve_workspace_size) exceed 16 MiB;
+ * are ordered.  A batch whose work lists (tsq_batch_evolve_workspace_size)
+ * exceed 16 MiB at the tile heights the library chooses takes taller tiles
+ * (one per resident wavefront, at least 2 K row pairs at K steps per pass),
+ * whose lists are shorter; the bits are the same.  Errors: those of
+ * tsq_batch_evolve; TSQ_ERR_WORKSPACE when the work lists exceed 16 MiB so too;
  * TSQ_ERR_DEVICE if the array's address cannot be found. */
 int tsq_batch_evolve_noalloc(tsq_plan* const* plans, void* const* psi_dev, void* const* ws,
                              const int64_t* steps, int32_t n, const tsq_schedule* schedule,

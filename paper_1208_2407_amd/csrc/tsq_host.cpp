@@ -765,7 +765,7 @@ int tsq_batch_evolve(tsq_plan* const* plans, void* const* psi, void* const* ws, 
                      int32_t n, const tsq_schedule* schedule, void* bws, size_t bws_bytes,
                      void* stream) {
     return tsq::batch_evolve_into(plans, psi, ws, steps, n, schedule, bws, bws_bytes, stream,
-                                  nullptr);
+                                  nullptr, false);
 }
 
 const char* tsq_last_error(void) { return g_err.c_str(); }
@@ -784,13 +784,13 @@ int tsq::set_error(int code, const char* fmt, ...) {
 
 int tsq::batch_evolve_into(tsq_plan* const* plans, void* const* psi, void* const* ws,
                            const int64_t* steps, int32_t n, const tsq_schedule* schedule,
-                           void* bws, size_t bws_bytes, void* stream, size_t* need) {
+                           void* bws, size_t bws_bytes, void* stream, size_t* need, bool coarse) {
     tsq_batch* b = nullptr;
     int rc = create_batch(plans, psi, ws, steps, n, schedule, false, &b);
     if (rc) return rc;
     size_t bytes = 0;
     tsq_batch_workspace_size(b, &bytes);
-    if (bytes > bws_bytes && !b->sched.segment_rows) {
+    if (coarse && bytes > bws_bytes && !b->sched.segment_rows) {
         tsq_batch_destroy(b);
         b = nullptr;
         rc = create_batch(plans, psi, ws, steps, n, schedule, true, &b);

@@ -346,10 +346,11 @@ int set_error(int code, const char* fmt, ...);
 // Build the batch of tsq_batch_create, copy its work lists to `bws` (at most
 // `bws_bytes`) and enqueue every pass on `stream`; `need` (if not null)
 // receives the work lists' size in bytes.  Shared by tsq_batch_evolve and its
-// workspace-free variant.
+// workspace-free variant; `coarse` (the latter, whose buffer cannot grow): tile heights
+// with shorter lists where the library's own outgrow the buffer.
 int batch_evolve_into(tsq_plan* const* plans, void* const* psi, void* const* ws,
                       const int64_t* steps, int32_t n, const tsq_schedule* schedule, void* bws,
-                      size_t bws_bytes, void* stream, size_t* need);
+                      size_t bws_bytes, void* stream, size_t* need, bool coarse);
 constexpr int kReduceThreads = 256;
 
 }  // namespace tsq

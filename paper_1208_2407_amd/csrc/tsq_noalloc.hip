@@ -51,7 +51,7 @@ extern "C" int tsq_batch_evolve_noalloc(tsq_plan* const* plans, void* const* psi
                               hipGetErrorString(e));
     size_t need = 0;
     const int rc = tsq::batch_evolve_into(plans, psi_dev, ws, steps, n, schedule, p, kScratchBytes,
-                                          stream, &need);
+                                          stream, &need, true);
     if (rc == TSQ_ERR_WORKSPACE && need > kScratchBytes)
         return tsq::set_error(TSQ_ERR_WORKSPACE,
                               "the batch's work lists take %zu bytes, more than the %zu bytes "
