@@ -418,6 +418,7 @@ struct tsq_batch {
     std::vector<BatchLaunch> launches;
     std::vector<BatchCopy> copies;
     std::vector<unsigned char> blob;  // host image of the device work lists
+    size_t counted = 0;               // their size with every job at kJobBytes
     char* bws = nullptr;              // device copy (after upload)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -427,9 +428,11 @@ struct tsq_batch {
 
 namespace {
 
-size_t blob_reserve(std::vector<unsigned char>& blob, size_t bytes) {
-    const size_t off = align_up(blob.size(), 256);
-    blob.resize(off + bytes);
+size_t blob_append(tsq_batch* b, const void* data, size_t bytes, size_t counted) {
+    const size_t off = align_up(b->blob.size(), 256);
+    b->blob.resize(off + bytes);
+    std::memcpy(b->blob.data() + off, data, bytes);
+    b->counted = align_up(b->counted, 256) + counted;
     return off;
 }
 
@@ -535,8 +538,8 @@ void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::Pa
     L.njobs = (int)jobs.size();
     L.ntiles = (int)tiles.size();
     L.nwaves = std::min(L.ntiles, slots);
-    L.jobs_off = blob_reserve(b->blob, jobs.size() * sizeof(tsq::BatchJob<R>));
-    std::memcpy(b->blob.data() + L.jobs_off, jobs.data(), jobs.size() * sizeof(tsq::BatchJob<R>));
+    L.jobs_off = blob_append(b, jobs.data(), jobs.size() * sizeof(tsq::BatchJob<R>),
+                             jobs.size() * tsq::kJobBytes<R>);
     // the steady passes of a batch walk the same tiles: one copy serves them all
     const size_t bytes = tiles.size() * sizeof(tsq::BatchTile);
     bool shared = false;
@@ -547,10 +550,7 @@ void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::Pa
         L.tiles_off = o.tiles_off;
         break;
     }
-    if (!shared) {
-        L.tiles_off = blob_reserve(b->blob, bytes);
-        std::memcpy(b->blob.data() + L.tiles_off, tiles.data(), bytes);
-    }
+    if (!shared) L.tiles_off = blob_append(b, tiles.data(), bytes, bytes);
     b->launches.push_back(L);
     b->total_tiles += L.ntiles;
 }
@@ -690,7 +690,7 @@ int tsq_batch_destroy(tsq_batch* b) {
 
 int tsq_batch_workspace_size(const tsq_batch* b, size_t* bytes) {
     if (!b || !bytes) return fail(TSQ_ERR_ARG, "null argument");
-    *bytes = align_up(b->blob.size(), 256) + 256;
+    *bytes = align_up(b->counted, 256) + 256;
     return ok();
 }
 

@@ -244,28 +244,27 @@ MarchArgs<R> make_march_args(const PassDesc& d, const MarchGeometry& g) {
 }
 
 // Job record of the batched kernel, uploaded to device memory: the launch
-// arguments a periodic static second-order pass uses.  Its size decides which
-// batches fit tsq_batch_evolve_noalloc's fixed array, so it stays what it was when
-// it held a whole MarchArgs (kJobBytes).
-template <class R>
-constexpr size_t kJobBytes = sizeof(R) == 4 ? 288 : 440;
+// arguments a periodic static second-order pass uses.
 template <class R>
 struct BatchJob {
     const void* src;
     void* dst;
     const void* ptab;
-    int nx, ny, strip_sites, seg_rows, nstrips, nsegs;
+    int nx, ny, strip_sites, seg_rows;
     R o1xs, o1xd, o1ys, o2xs, o2ys, ehxs, ehys, c1xs, c1xd, c1ys;
-    unsigned char unused[kJobBytes<R> - 3 * 8 - 6 * 4 - 10 * sizeof(R)];
 };
-static_assert(sizeof(BatchJob<float>) == kJobBytes<float> && sizeof(BatchJob<double>) == kJobBytes<double>,
-              "job records of the stated size");
+// Bytes a job counts for in the size of a batch's work lists, which decides which
+// batches tsq_batch_evolve_noalloc takes and how large callers' buffers are: what a
+// whole MarchArgs took, so that both stay what they were.
+template <class R>
+constexpr size_t kJobBytes = sizeof(R) == 4 ? 288 : 440;
+static_assert(sizeof(BatchJob<float>) <= kJobBytes<float> && sizeof(BatchJob<double>) <= kJobBytes<double>,
+              "a job record takes no more than it counts for");
 template <class R>
 BatchJob<R> batch_job(const MarchArgs<R>& a) {
     BatchJob<R> j = {};
     j.src = a.src; j.dst = a.dst; j.ptab = a.ptab;
     j.nx = a.nx; j.ny = a.ny; j.strip_sites = a.strip_sites; j.seg_rows = a.seg_rows;
-    j.nstrips = a.nstrips; j.nsegs = a.nsegs;
     j.o1xs = a.o1xs; j.o1xd = a.o1xd; j.o1ys = a.o1ys;
     j.o2xs = a.o2xs; j.o2ys = a.o2ys;
     j.ehxs = a.ehxs; j.ehys = a.ehys;

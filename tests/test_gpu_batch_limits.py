@@ -34,3 +34,31 @@ def test_a_short_buffer_is_refused():
     tsq.tsq_batch_evolve(*args, steps, sc, base, need, stream)
     torch.cuda.synchronize()
     assert not any(torch.equal(x, y) for x, y in zip(psis, before))
+
+
+@pytest.mark.parametrize("dtype,record,counted", [("c64", 80, 288), ("c128", 120, 440)])
+def test_job_records_carry_no_padding_and_count_as_before(dtype, record, counted):
+    n = 10
+    tdt = torch.complex64 if dtype == "c64" else torch.complex128
+    plans, psis = [], []
+    for _ in range(n):
+        plan = tsq.Plan(64, 64, 0.05, dtype)
+        plan.set_potential(torch.zeros(64, 64, dtype=torch.float64, device="cuda"))
+        plans.append(plan)
+        psis.append(torch.ones(64, 64, dtype=tdt, device="cuda"))
+    batch = tsq.tsq_batch_create([p.handle for p in plans], [x.data_ptr() for x in psis],
+                                 [p.workspace().data_ptr() for p in plans], [1] * n, tsq.tsq_schedule(5, 0, 1, 1))
+    launches, tiles = tsq.tsq_batch_info(batch)
+    need = tsq.tsq_batch_workspace_size(batch)
+
+    def up(v):
+        return (v + 255) // 256 * 256
+
+    assert launches == 1 and need == up(up(n * counted) + 16 * tiles) + 256
+    buf = torch.full((need + 256,), 0xab, dtype=torch.uint8, device="cuda")
+    base = (buf.data_ptr() + 255) // 256 * 256
+    tsq.tsq_batch_upload(batch, base, need, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    written = buf[base - buf.data_ptr():].cpu().numpy()
+    assert (written[up(n * record) + 16 * tiles:] == 0xab).all()
+    tsq.tsq_batch_destroy(batch)
