@@ -813,6 +813,27 @@ int tsq::set_error(int code, const char* fmt, ...) {
     return code;
 }
 
+long long tsq::slab_segment_pairs(long long columns, long long pairs, int stages, long long cus) {
+    double best = 0.0;
+    long long best_q = 1;
+    for (long long segs = 1; segs <= pairs;) {
+        const long long q = (pairs + segs - 1) / segs;
+        const long long tiles = columns * ((pairs + q - 1) / q);
+        const long long rounds = (tiles + cus - 1) / cus;
+        const double cost = (double)rounds * (double)(q + 2 * stages - 1) +
+                            (double)(tiles * (q + 2 * stages)) / (double)cus;
+        if (segs == 1 || cost < best) {
+            best = cost;
+            best_q = q;
+        }
+        // neither term of more segments can be less than this
+        if ((double)columns * (double)(2 * pairs + 2 * stages * segs) / (double)cus > best) break;
+        if (q <= 1) break;
+        segs = (pairs + q - 2) / (q - 1);  // the next that changes q
+    }
+    return best_q;
+}
+
 int tsq::batch_evolve_into(tsq_plan* const* plans, void* const* psi, void* const* ws,
                            const int64_t* steps, int32_t n, const tsq_schedule* schedule,
                            void* bws, size_t bws_bytes, void* stream, size_t* need, bool coarse) {
@@ -1260,31 +1281,12 @@ struct SlabPass {
     int stages, rp, seg_pairs;
 };
 
-// Plane pairs per tile: the blocks go in rounds of one per compute unit, each
-// marching a tile's Q pairs and its halo (a pair per stage and side, half of them
-// without the second stage), and every tile reads its halo: the segment count
-// with the least sum of the two, in pairs per unit.  At 512^3 complex64 two
-// segments (220 tiles on 256 units).
 SlabPass slab_pass(const tsq_plan* p, int stages, int rp, long long cus) {
-    SlabPass r{stages, rp, 1};
-    const long long columns = tsq::slab_columns(p->p.nx, p->p.ny, stages, rp).columns;
     const long long pairs = p->p.nz / 2;
-    double best = 0.0;
-    for (long long segs = 1; segs <= pairs; ++segs) {
-        const long long q = (pairs + segs - 1) / segs;
-        const long long tiles = columns * ((pairs + q - 1) / q);
-        const long long rounds = (tiles + cus - 1) / cus;
-        const double cost = (double)rounds * (double)(q + 2 * stages - 1) +
-                            (double)(tiles * (q + 2 * stages)) / (double)cus;
-        if (segs == 1 || cost < best) {
-            best = cost;
-            r.seg_pairs = (int)q;
-        }
-        if (q <= 1) break;
-    }
     if (p->sched.segment_rows > 0)
-        r.seg_pairs = (int)std::min<long long>(pairs, p->sched.segment_rows / 2);
-    return r;
+        return {stages, rp, (int)std::min<long long>(pairs, p->sched.segment_rows / 2)};
+    const long long columns = tsq::slab_columns(p->p.nx, p->p.ny, stages, rp).columns;
+    return {stages, rp, (int)tsq::slab_segment_pairs(columns, pairs, stages, cus)};
 }
 
 // Three-dimensional mesh by the slab march: passes of two steps (small meshes:
@@ -1316,7 +1318,6 @@ int run_slab(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) 
     // | 30.4, 512^3 1515 | 1138.
     const bool two_steps = plan->sites >= 1500000;
     const int rp = plan->p.dtype == TSQ_C64 && plan->sites >= 6000000 ? 2 : 1;
-    const SlabPass one = slab_pass(plan, 1, 1, cus), two = slab_pass(plan, 2, rp, cus);
     const int64_t pairs2 = two_steps ? steps / 2 : 0;  // two-step passes
     int64_t ones = steps - 2 * pairs2;               // single-step passes before the closing
     // an odd count's last step takes the closing factors along where that leaves
@@ -1324,6 +1325,8 @@ int run_slab(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) 
     const bool along = two_steps && ones == 1 && ((pairs2 + 1) & 1) == 0;
     if (along) ones = 0;
     const int64_t passes = pairs2 + ones + (along ? 1 : 0);
+    const SlabPass one = ones ? slab_pass(plan, 1, 1, cus) : SlabPass{1, 1, 1};
+    const SlabPass two = pairs2 || along ? slab_pass(plan, 2, rp, cus) : SlabPass{2, rp, 1};
     for (int64_t i = 0; i < passes; ++i) {
         const SlabPass& k = i < pairs2 || along ? two : one;
         d.src = buf[i & 1];

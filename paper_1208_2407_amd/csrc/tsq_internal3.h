@@ -73,6 +73,14 @@ inline SlabColumns slab_columns(int nx, int ny, int stages, int rp) {
     }
     return g;
 }
+// Plane pairs per tile of the slab march: the blocks go in rounds of one per compute
+// unit, each marching a tile's Q pairs and its halo (a pair per stage and side, half of
+// them without the second stage), and every tile reads its halo: the segment count with
+// the least sum of the two, in pairs per unit.  At 512^3 complex64 two segments (186 tiles
+// on 256 units).  Segment counts that give the same Q are passed over, and the search
+// ends where no larger count can win: a few hundred counts for the longest mesh
+// (2 x 2 x 2^29) instead of its 2^28, which took 2.9 s of every call.
+long long slab_segment_pairs(long long columns, long long pairs, int stages, long long cus);
 // log of the squared modulus a step's tangent-form factors multiply a site by.
 template <class R>
 double step3_log_sec2(const Coef64* oh, const Coef64* o2) {
