@@ -46,6 +46,7 @@ struct PassDesc {
 
 constexpr int kMaxSteps = 8;     // deepest fusion (phase ring in LDS)
 constexpr int kMaxRegSteps = 6;  // deepest fusion with the phase ring in registers
+constexpr int kScalarRowSteps = 6;  // see march_phase_lds
 constexpr int kMaxRegSteps2 = 4; // ... with two x-pairs per lane
 constexpr int kMaxTdSteps = 6;   // deepest fusion with a time-dependent potential
 constexpr int kTurns = 2048;     // time-dependent phase: factors exp(-i j pi/1024), j mod 2048
@@ -287,11 +288,12 @@ int march_blocks_per_cu(int dtype, int steps, bool last, int pairs_per_lane, boo
 bool march_variant_exists(int dtype, int steps, bool last, int pairs_per_lane, bool phase_lds,
                           bool closed = false, bool td = false);
 
-// Whether a static periodic second-order pass keeps 64-bit addresses per lane: the
-// complex64 march of one mesh addresses rows by the scalar unit and a lane's site by a
-// 32-bit byte offset within its row, so rows of more than 4 GiB (only 2 x more than 2^29
-// sites are that long) run the instances without it (Variant::Lanes; the same bits).
-bool lane_addresses(int dtype, int nx);
+// Where a pass keeps its phases: as scheduled, but for the one instance that addresses
+// rows by the scalar unit and a lane's site by a 32-bit byte offset within its row (static
+// periodic complex64, the closing pass of kScalarRowSteps steps, register phases, one pair
+// per lane).  Rows of more than 4 GiB (only 2 x more than 2^29 sites are that long) run
+// its LDS form, which has lane addresses; the same bits.
+bool march_phase_lds(int dtype, int nx, int steps, bool last, int pairs_per_lane, bool phase_lds);
 
 // All launchers return hipSuccess or the launch error.
 // exp(-i dt (V + eps0) / hbar) times `scale` per site.

@@ -23,14 +23,13 @@ const void* march_ptr_c128_closedtd(int steps, bool last, int ppl, bool lds);
 const void* march_ptr_c64_closedtd(int steps, bool last, int ppl, bool lds);
 const void* march_ptr_c128_order4(int steps, bool last, int ppl, bool lds);
 const void* march_ptr_c64_order4(int steps, bool last, int ppl, bool lds);
-const void* march_ptr_c64_lanes(int steps, bool last, int ppl, bool lds);
 // Tile kernels (tile_<dtype>.hip)
 const void* tile_ptr_c128(int pairs_per_wave, bool closed, bool td, bool u4);
 const void* tile_ptr_c64(int pairs_per_wave, bool closed, bool td, bool u4);
 
 namespace {
 
-enum class Variant { Single, Batch, Closed, TimeDep, ClosedTimeDep, Order4, Lanes };
+enum class Variant { Single, Batch, Closed, TimeDep, ClosedTimeDep, Order4 };
 
 const void* march_kernel_ptr(int dtype, int steps, bool last, int ppl, bool lds, Variant v) {
     const bool d = dtype == 1;
@@ -48,8 +47,6 @@ const void* march_kernel_ptr(int dtype, int steps, bool last, int ppl, bool lds,
                      : march_ptr_c64_closedtd(steps, last, ppl, lds);
         case Variant::Order4:
             return d ? march_ptr_c128_order4(steps, last, ppl, lds) : march_ptr_c64_order4(steps, last, ppl, lds);
-        case Variant::Lanes:
-            return d ? nullptr : march_ptr_c64_lanes(steps, last, ppl, lds);
     }
     return nullptr;
 }
@@ -155,19 +152,17 @@ hipError_t launch_batch(int dtype, int steps, bool last, int pairs_per_lane, boo
     return hipGetLastError();
 }
 
-bool lane_addresses(int dtype, int nx) {
+bool march_phase_lds(int dtype, int nx, int steps, bool last, int pairs_per_lane, bool phase_lds) {
     const long long site = 8;  // the farthest lane's pair starts at column nx - 2
-    return dtype == 0 && (nx - 2) * site > 0xffffffffLL;
+    return phase_lds || (dtype == 0 && steps == kScalarRowSteps && last && pairs_per_lane == 1 &&
+                         (nx - 2) * site > 0xffffffffLL);
 }
 
 hipError_t launch_pass(int dtype, const PassDesc& pass, hipStream_t s) {
     PassDesc d = pass;
-    Variant v = variant_of(false, d.closed, d.td, d.u4);
-    if (v == Variant::Single && lane_addresses(dtype, d.nx)) {
-        v = Variant::Lanes;
-        d.pairs_per_lane = 1;
-        d.phase_lds = d.steps > kMaxRegSteps;
-    }
+    const Variant v = variant_of(false, d.closed, d.td, d.u4);
+    if (v == Variant::Single)
+        d.phase_lds = march_phase_lds(dtype, d.nx, d.steps, d.last, d.pairs_per_lane, d.phase_lds);
     const void* f = march_kernel_ptr(dtype, d.steps, d.last, d.pairs_per_lane, d.phase_lds, v);
     if (!f) return hipErrorInvalidValue;
     hipError_t e = dtype == 1 ? launch_with<double>(f, d, s) : launch_with<float>(f, d, s);

@@ -218,9 +218,9 @@ struct Row {
     R im[SPL];
 };
 
-// Load / store one x-pair (2 sites starting at even column `x`) of row `r`.  The
-// march gives them the row's (wavefront-uniform) address and the lane's byte
-// offset within it: the scalar unit steps the address and a load takes no vector
+// Load / store one x-pair (2 sites starting at even column `x`) of row `r`.  Where
+// the row's (wavefront-uniform) address and the lane's byte offset within it are
+// given apart, the scalar unit steps the address and a load takes no vector
 // instruction but itself.
 template <int SPL>
 __device__ __forceinline__ void load_pair(const void* base, long long off, Row<double, SPL>& row, int p) {
@@ -656,12 +656,17 @@ using PhaseT = std::conditional_t<TD, double2, typename T::PT>;
 template <class T, bool TD>
 using TableT = std::conditional_t<TD, double2, typename T::TT>;
 
-// UA (complex64, one problem, static, second order): rows are addressed by
-// the scalar unit, see load_pair; a lane's offset within its row has 32 bits
-// (lane_addresses names the rows that are too long).  At 32768^2 the 6-step pass, bound by its
-// vector instructions, takes 5.6% less time; the marches bound by memory and the
-// batched one, whose row addresses come from a job record, run 1 to 2% slower
-// that way and keep per-lane addresses.
+// UA: rows are addressed by the scalar unit, see load_pair; a lane's offset within its
+// row has 32 bits (march_phase_lds keeps longer rows from such an instance).  Only the
+// closing complex64 pass of 6 steps with register phases takes it (kScalarRows): it needs
+// 256 registers that way and 258 with lane addresses, which leaves one wavefront per
+// SIMD for two (6 steps of 4096^2, closing pass included, 615 us against 642; 100 x 60000
+// 393 against 511).  Everywhere else it only lengthens the chain of a wavefront: lane
+// addresses are 0 to 7% faster (4096^2 at 8 steps 1178 us against 1263, 2048^2 at 5 198.5
+// against 201.6, 1030 x 614 at 5 84.8 against 88.4).
+template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4>
+constexpr bool kScalarRows = sizeof(typename T::R) == 4 && S == kScalarRowSteps && LAST && PPL == 1 && !LDS &&
+                             !CLOSED && !TD && !U4;
 template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4, bool UA>
 __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, int strip, int seg,
                                            bool rev, int lane, PhaseT<T, TD>* ring,
@@ -964,8 +969,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<typename T::R>& a, in
 }
 
 // One problem, one tile per wavefront.
-template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4 = false,
-          bool UA = sizeof(typename T::R) == 4 && !CLOSED && !TD && !U4>
+template <class T, int S, bool LAST, int PPL, bool LDS, bool CLOSED, bool TD, bool U4 = false>
 __global__ void __launch_bounds__(kWaveSize * kWavesPerBlock)
 march_kernel(const MarchArgs<typename T::R> a) {
     __shared__ WaveRing<PhaseT<T, TD>, S, PPL, LDS> rings[LDS ? kWavesPerBlock : 1];
@@ -1000,6 +1004,7 @@ march_kernel(const MarchArgs<typename T::R> a) {
     const int grp = lb - seg * ngroups;
     const int strip = grp * kWavesPerBlock + wave;
     if (strip >= a.nstrips) return;  // uniform per wavefront
+    constexpr bool UA = kScalarRows<T, S, LAST, PPL, LDS, CLOSED, TD, U4>;
     march_tile<T, S, LAST, PPL, LDS, CLOSED, TD, U4, UA>(a, strip, seg, seg & 1, lane,
                                                  &rings[LDS ? wave : 0].v[0][0][0][lane], turns);
 }
@@ -1036,9 +1041,8 @@ march_batch_kernel(const BatchJob<typename T::R>* __restrict__ jobs,
 // 1..kMaxSteps (1 pair per lane), single and batched; closed meshes: both
 // rings with 1 pair per lane, single only; time-dependent potentials
 // (periodic or closed): both rings, 1 pair per lane, at most kMaxTdSteps
-// steps per pass, single only; complex64 with lane addresses (see
-// lane_addresses): 1 pair per lane, LDS ring beyond kMaxRegSteps only.
-enum class Variant { Single, Batch, Closed, TimeDep, ClosedTimeDep, Order4, Lanes };
+// steps per pass, single only.
+enum class Variant { Single, Batch, Closed, TimeDep, ClosedTimeDep, Order4 };
 
 template <class T, int S, bool LAST, int PPL, bool LDS, Variant V>
 const void* kernel_ptr() {
@@ -1053,12 +1057,7 @@ const void* kernel_ptr() {
         return reinterpret_cast<const void*>(&march_batch_kernel<T, S, LAST, PPL, LDS>);
     else if constexpr (PPL != 1)
         return nullptr;
-    else if constexpr (V == Variant::Lanes) {
-        if constexpr (LDS == (S > kMaxRegSteps))
-            return reinterpret_cast<const void*>(&march_kernel<T, S, LAST, 1, LDS, false, false, false, false>);
-        else
-            return nullptr;
-    } else if constexpr (V == Variant::Closed)
+    else if constexpr (V == Variant::Closed)
         return reinterpret_cast<const void*>(&march_kernel<T, S, LAST, PPL, LDS, true, false>);
     else if constexpr (V == Variant::TimeDep)
         return reinterpret_cast<const void*>(&march_kernel<T, S, LAST, PPL, LDS, false, true>);

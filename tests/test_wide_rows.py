@@ -1,9 +1,10 @@
-"""Rows of more than 4 GiB: the complex64 march addresses a lane's site by a 32-bit byte
-offset within its row, so meshes wider than 2^29 sites (only 2 rows of them make a legal
-plan) take instances with 64-bit lane addresses.  Which meshes do is host logic; on the
-GPU such a mesh holds two packets, one across column 2^29 and one across the wrap, each
-of which must evolve as on a small mesh, to the bit, with exact zeros elsewhere."""
+"""Rows of more than 4 GiB: one instance of the complex64 march addresses a lane's site by a
+32-bit byte offset within its row, so meshes wider than 2^29 sites (only 2 rows of them
+make a legal plan) must not take it.  Which passes do is host logic; on the GPU such a
+mesh holds two packets, one across column 2^29 and one across the wrap, each of which
+must evolve as on a small mesh, to the bit, with exact zeros elsewhere."""
 import ctypes
+import itertools
 
 import pytest
 import torch
@@ -14,21 +15,23 @@ EDGE = 1 << 29
 
 
 def test_rows_beyond_the_lane_offsets_keep_lane_addresses():
-    rule = ctypes.CDLL(tsq.library_path())._ZN3tsq14lane_addressesEii  # tsq::lane_addresses(dtype, nx)
+    # tsq::march_phase_lds(dtype, nx, steps, last, pairs_per_lane, phase_lds)
+    rule = ctypes.CDLL(tsq.library_path())._ZN3tsq15march_phase_ldsEiiibib
+    rule.argtypes = [ctypes.c_int] * 3 + [ctypes.c_bool, ctypes.c_int, ctypes.c_bool]
     rule.restype = ctypes.c_bool
-    c64, c128 = 0, 1
-    for nx in (2, 4096, EDGE - 2, EDGE):
-        assert not rule(c64, nx) and (nx - 2) * 8 < 1 << 32
-    for nx in (EDGE + 2, 2 * EDGE - 2):
-        assert rule(c64, nx) and (nx - 2) * 8 >= 1 << 32
-    assert not any(rule(c128, nx) for nx in (2, EDGE, EDGE + 2, 2 * EDGE - 2))  # has them anyway
+    for nx in (2, 4096, EDGE - 2, EDGE, EDGE + 2, 2 * EDGE - 2):
+        wide = (nx - 2) * 8 >= 1 << 32
+        assert wide == (nx > EDGE)
+        for dtype, S, last, ppl, lds in itertools.product((0, 1), range(1, 9), (False, True), (1, 2), (False, True)):
+            scalar_rows = dtype == 0 and S == 6 and last and ppl == 1 and not lds
+            assert rule(dtype, nx, S, last, ppl, lds) == (lds or (wide and scalar_rows))
     # the longest legal row: two of them make 2^31 - 4 sites
     tsq.Plan(2 * EDGE - 2, 2, 0.05, "c64")
 
 
 @pytest.mark.gpu
 def test_wide_mesh_evolves_as_small_ones():
-    nx, ny, W, steps = EDGE + 4096, 2, 1024, 9  # light cone: 2 * 9 + 1 columns per side
+    nx, ny, W, steps = EDGE + 4096, 2, 1024, 12  # light cone: 2 * 12 + 1 columns per side
     gen = torch.Generator().manual_seed(7)
     psi0 = torch.zeros(ny, W, dtype=torch.complex64)
     psi0[:, 64:-64] = torch.randn(ny, W - 128, dtype=torch.complex64, generator=gen)
@@ -47,7 +50,7 @@ def test_wide_mesh_evolves_as_small_ones():
         n = min(W, nx - x0)
         V[:, x0:x0 + n], V[:, :W - n] = V0[:, :n].cuda(), V0[:, n:].cuda() if n < W else 0.0
     plan.set_potential(V)
-    for schedule in ((0, 0, 0, 0), (6, 0, 1, 2), (8, 0, 1, 2), (3, 0, 2, 1), (1, 0, 1, 1)):
+    for schedule in ((0, 0, 0, 0), (6, 0, 1, 1), (8, 0, 1, 2), (3, 0, 2, 1), (1, 0, 1, 1)):
         psi.zero_()
         for x0 in starts:
             n = min(W, nx - x0)
