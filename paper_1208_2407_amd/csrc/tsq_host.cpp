@@ -108,6 +108,8 @@ bool resolve_schedule(const tsq_schedule& in, tsq_schedule& out) {
     return true;
 }
 
+constexpr int kUnits = 256;  // compute units of an MI355X
+
 struct DeviceShape {
     int device = -1;
     int cus = 0;
@@ -163,13 +165,11 @@ int occupancy_cached(int dtype, int steps, bool last, int ppl, bool lds, bool cl
 // The height with the least of that: 1030 x 614 complex64 at 5 steps per pass
 // takes 8 rows, 13.9 us a pass against 20.8 at 2K pairs (6 rows, two blocks on
 // some units: 17.3); 256^2 takes 2 rows, 10.1 against 18.9 us.
-int default_seg_rows(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool closed,
-                     bool td, bool u4 = false) {
+// `cus` compute units, `occ` resident blocks on one.
+int seg_rows_on(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool closed, bool td,
+                int cus, int occ) {
     const tsq::MarchGeometry g = tsq::march_geometry(p->p.nx, p->p.ny, steps, last, ppl, 2);
-    int cus = device_cus();
-    if (cus <= 0) cus = 256;
     const bool c128 = p->p.dtype == TSQ_C128;
-    const int occ = occupancy_cached(p->p.dtype, steps, last, ppl, lds, closed, td, u4);
     const long long pairs = (p->p.ny + 1) / 2, K = steps + (last ? 1 : 0);
     // a launch has one block per segment of kWavesPerBlock strips
     const long long groups = (g.nstrips + tsq::kWavesPerBlock - 1) / tsq::kWavesPerBlock;
@@ -194,6 +194,14 @@ int default_seg_rows(const tsq_plan* p, int steps, bool last, int ppl, bool lds,
         }
     }
     return (int)(2 * q);
+}
+
+int default_seg_rows(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool closed,
+                     bool td, bool u4 = false) {
+    int cus = device_cus();
+    if (cus <= 0) cus = kUnits;
+    return seg_rows_on(p, steps, last, ppl, lds, closed, td, cus,
+                       occupancy_cached(p->p.dtype, steps, last, ppl, lds, closed, td, u4));
 }
 
 // Fourth order on a periodic 2D mesh runs one pass per fourth-order step (its
@@ -324,14 +332,16 @@ int64_t tile_steps_before(const TilePasses& t, int64_t steps, int64_t i) {
 // SIMD (see default_seg_rows).  Both sides at 200+ steps, us per step, march
 // against tile: 64^2 1.98 : 1.17, 512^2 2.25 : 1.34, 1030 x 614 2.72 : 1.65
 // (complex128 2.75 : 2.14), 1500^2 4.6 : 4.3; beyond two blocks per unit the
-// march is the faster.
+// march is the faster.  The estimate takes an MI355X's 256 units, and of the march the
+// blocks of its 5-step passes that fit one (complex64 two, driven between walls one;
+// complex128 one), instead of asking the device: tsq_evolve_passes counts these passes
+// and is host only.
 TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
     TilePasses best;
     if (!p->sched_default || p->three_d || steps < 1) return best;
     const bool u4 = fused_order4(p);
     if (p->p.order == 4 && !u4) return best;  // closed fourth order runs kind by kind
-    int cus = device_cus();
-    if (cus <= 0) cus = 256;
+    const int cus = kUnits;
     // the tallest tiles at the fewest stages: no more blocks per unit than two, or never
     if (tsq::tile_geometry(p->p.nx, p->p.ny, 2, false, 2).tiles > 2LL * cus) return best;
     const double launch = 2.2;
@@ -341,7 +351,8 @@ TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
     const int S0 = u4 ? 5 : td ? std::min(p->sched.steps_per_pass, tsq::kMaxTdSteps)
                                : p->sched.steps_per_pass;
     const bool lds0 = u4 || p->sched.phase_store == 2;
-    const int rows0 = default_seg_rows(p, S0, false, 1, lds0, closed, td, u4);
+    const int occ0 = p->p.dtype == TSQ_C128 || (closed && td) ? 1 : 2;
+    const int rows0 = seg_rows_on(p, S0, false, 1, lds0, closed, td, cus, occ0);
     const tsq::MarchGeometry g0 = tsq::march_geometry(p->p.nx, p->p.ny, S0, false, 1, rows0);
     const int64_t n0 = (g0.blocks + cus - 1) / cus;
     const double march = launch + 0.22 * S0 * (rows0 / 2 + S0) *
@@ -1296,7 +1307,7 @@ int run_slab(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream_t s) 
     char* w = static_cast<char*>(ws);
     void* buf[2] = {psi, w + plan->off_psi2};
     int cus = device_cus();
-    if (cus <= 0) cus = 256;
+    if (cus <= 0) cus = kUnits;
     tsq::Pass3Desc d;
     d.ptab = w + plan->kind[0].off_ptab;
     d.nx = plan->p.nx;
@@ -1353,7 +1364,7 @@ int run_evolution3(tsq_plan* plan, void* psi, int64_t steps, void* ws, hipStream
     char* w = static_cast<char*>(ws);
     void* buf[2] = {psi, w + plan->off_psi2};
     int cus = device_cus();
-    if (cus <= 0) cus = 256;
+    if (cus <= 0) cus = kUnits;
     tsq::Pass3Desc d;
     d.ptab = w + plan->kind[0].off_ptab;
     d.nx = plan->p.nx;
