@@ -143,9 +143,11 @@ typedef struct {
 } tsq_schedule;
 /* With every field 0 (also a new plan's schedule) the library may run a small
  * 2D mesh, up to about 1000^2 sites, in tile kernels instead of the march:
- * every row pair of a block works on a step at once, 1..14 steps per pass
+ * every row pair of a block works on a step at once, 1..15 steps per pass
  * dealt evenly over the passes, the same bits.  tsq_evolve_passes counts them;
- * tsq_plan_get_schedule still returns the march's defaults. */
+ * tsq_plan_get_schedule still returns the march's defaults.  Setting those
+ * defaults explicitly is the march, also on a small mesh: to leave the choice
+ * to the library, set zeros. */
 
 /* Set the plan's schedule (host only).  Zero fields take their defaults;
  * tsq_plan_get_schedule returns the resolved values (segment_rows stays 0 when
