@@ -145,6 +145,25 @@ def roofline(dtype: str, sites: int, launch_s: float, site_steps_per_s: float, t
     return out
 
 
+def passes_report(plan, steps: int, left_to_library: bool) -> dict:
+    """Kernel, schedule and passes of one evolution of an order-2 2D plan.  A small mesh
+    left to the library runs in the tile kernels, which no schedule names: its passes
+    differ from the march's under the schedule the plan reports."""
+    sched = plan.schedule()
+    passes, copy_back = plan.passes(steps)
+    tile = False
+    if left_to_library:
+        plan.set_schedule(*sched)
+        tile = plan.passes(steps) != (passes, copy_back)
+        plan.set_schedule(0, 0, 0, 0)
+    if tile:
+        return {"kernel": "tile_kernel", "steps_per_pass": round(steps / passes, 2),
+                "passes_per_solve": passes, "copy_back": copy_back}
+    return {"kernel": "march_kernel", "steps_per_pass": sched[0], "segment_rows": sched[1],
+            "pairs_per_lane": sched[2], "phase_store": {1: "registers", 2: "lds"}[sched[3]],
+            "passes_per_solve": passes, "copy_back": copy_back}
+
+
 def run_dtype(dtype: str, p, psi0, V, args, order: int = 2, bc: str = "periodic",
               keep_result: bool = False):
     """Tune, then time args.steps whole solves (phase table + p.steps fused steps
@@ -160,15 +179,17 @@ def run_dtype(dtype: str, p, psi0, V, args, order: int = 2, bc: str = "periodic"
     plan = tsq.Plan(p.nx, p.ny, p.dt, dtype, order=order, bc=bc, device=psi.device)
     plan.set_potential(V)
     tuning = None
+    sched = (0, 0, 0, 0)
     if args.schedule:
-        plan.set_schedule(*[int(v) for v in args.schedule.split(",")])
+        sched = tuple(int(v) for v in args.schedule.split(","))
+        plan.set_schedule(*sched)
     elif not args.no_tune:
         sched, table = autotune.tune(plan, psi, log=log if args.verbose else None)
         tuning = {"table_ms": table, "tie": autotune.TIE}
         log(f"{dtype} {p.nx}x{p.ny}: autotuned schedule S={sched[0]} seg={sched[1]} "
             f"ppl={sched[2]} store={sched[3]}")
-    sched = plan.schedule()
-    passes, copy_back = plan.passes(p.steps)
+    report = passes_report(plan, p.steps, sched == (0, 0, 0, 0))
+    sched, passes = plan.schedule(), report["passes_per_solve"]
     stream = torch.cuda.current_stream()
 
     def solve(events=None):
@@ -195,7 +216,7 @@ def run_dtype(dtype: str, p, psi0, V, args, order: int = 2, bc: str = "periodic"
     launch_s = evolve_ms * 1e-3 / (args.steps * passes)
     # counters were taken on second-order periodic passes only
     traffic = (committed_traffic(dtype, sched, p.nx, p.ny)
-               if order == 2 and bc == "periodic" else None)
+               if order == 2 and bc == "periodic" and report["kernel"] == "march_kernel" else None)
     # precision: one solve from the initial state
     psi.copy_(psi0)
     n0, e0 = plan.observables(psi, V)
@@ -206,12 +227,10 @@ def run_dtype(dtype: str, p, psi0, V, args, order: int = 2, bc: str = "periodic"
     out = {
         "value": site_steps / wall,
         "ms_per_step": wall / args.steps * 1e3,
-        "schedule": {"steps_per_pass": sched[0], "segment_rows": sched[1],
-                     "pairs_per_lane": sched[2],
-                     "phase_store": {1: "registers", 2: "lds"}[sched[3]],
-                     "passes_per_solve": passes, "copy_back": copy_back},
+        "schedule": report,
         # a fourth-order pass on a periodic mesh reads both sub-step tables
         "roofline": roofline(dtype, p.nx * p.ny, launch_s, site_steps / wall, traffic,
+                             kernel=report["kernel"],
                              tables=2 if order == 4 and bc == "periodic" else 1),
         "precision": {"norm_start": n0, "norm_end": n1, "norm_drift": n1 - n0,
                       "energy_start": e0, "energy_end": e1, "energy_drift": e1 - e0},
@@ -255,10 +274,11 @@ def run_td(dtype: str, p, psi0, V0, W, f, args, bc: str = "periodic"):
     plan.set_potential_td(V0, W)
     if args.schedule:
         plan.set_schedule(*[int(v) for v in args.schedule.split(",")])
+        report = passes_report(plan, len(f), False)
     else:
-        autotune.tune_td(plan, psi, f[:120], log=log if args.verbose else None)
-    sched = plan.schedule()
-    passes, copy_back = plan.passes(len(f))
+        picked, _ = autotune.tune_td(plan, psi, f[:120], log=log if args.verbose else None)
+        report = passes_report(plan, len(f), picked == autotune.LIBRARY_REPORTS)
+    sched, passes = plan.schedule(), report["passes_per_solve"]
     V_end = V0 + float(f[-1]) * W   # potential at the last step's midpoint, for the energy
 
     def solve(events=None):
@@ -292,10 +312,7 @@ def run_td(dtype: str, p, psi0, V0, W, f, args, bc: str = "periodic"):
         f"{site_steps / wall:.4e} site-steps/s, pass {launch_s * 1e6:.1f} us, norm {norm:.15f}")
     return {
         "value": site_steps / wall, "ms_per_step": wall / args.steps * 1e3,
-        "schedule": {"steps_per_pass": sched[0], "pairs_per_lane": sched[2],
-                     "phase_store": {1: "registers", 2: "lds"}[sched[3]],
-                     "passes_per_solve": passes, "copy_back": copy_back,
-                     "picked_by": "given" if args.schedule else "autotune.tune_td"},
+        "schedule": {**report, "picked_by": "given" if args.schedule else "autotune.tune_td"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
                      "algorithmic_bytes_per_launch": alg_bytes,
