@@ -164,8 +164,9 @@ int tsq_plan_get_schedule(const tsq_plan* plan, tsq_schedule* schedule);
  * (odd pass count that cannot be split).  Order-4 plans of periodic 2D meshes
  * run one pass per fourth-order step (its five second-order sub-steps fused,
  * whatever steps_per_pass says).  A 3D mesh is counted as one pass per step and
- * a closing one, steps + 1, whether or not its passes fuse two steps.  Host
- * only.  Errors: TSQ_ERR_ARG. */
+ * a closing one, steps + 1, with a copy if that is odd, though its passes may
+ * fuse two steps and its closing one writes psi itself.  Host only.  Errors:
+ * TSQ_ERR_ARG. */
 int tsq_evolve_passes(const tsq_plan* plan, int64_t steps, int64_t* passes, int32_t* copy_back);
 
 /* The diagonal part H0 of Sec. 2 (potential plus the mesh's on-site term

@@ -312,16 +312,24 @@ class Plan:
 
     def set_schedule(self, steps_per_pass: int = 0, segment_rows: int = 0,
                      pairs_per_lane: int = 0, phase_store: int = 0) -> None:
-        """Zero fields take the library defaults; phase_store 1 = registers, 2 = LDS."""
+        """Zero fields take the library defaults; phase_store 1 = registers, 2 = LDS.
+        All zero leaves the choice to the library (tile kernels on small 2D meshes,
+        else 5 steps per pass); the values schedule() then reports, set explicitly,
+        are the march on any mesh."""
         tsq_plan_set_schedule(self.handle, tsq_schedule(int(steps_per_pass), int(segment_rows),
                                                         int(pairs_per_lane), int(phase_store)))
 
     def schedule(self) -> Tuple[int, int, int, int]:
-        """(steps_per_pass, segment_rows, pairs_per_lane, phase_store) in force."""
+        """(steps_per_pass, segment_rows, pairs_per_lane, phase_store) of the march as
+        in force; small 2D meshes under all-zero fields may run in the tile kernels,
+        which no schedule names: hand set_schedule zeros, not these values, to another
+        plan."""
         return tsq_plan_get_schedule(self.handle).as_tuple()
 
     def passes(self, steps: int) -> Tuple[int, bool]:
-        """(kernel launches, trailing copy) that evolve(psi, steps) makes."""
+        """(kernel launches, trailing copy) that evolve(psi, steps) makes on a 2D mesh;
+        a 3D mesh reports (steps + 1, steps even), the bookkeeping of one step per pass
+        and a closing one, whatever its passes fuse."""
         return tsq_evolve_passes(self.handle, steps)
 
     def workspace(self):
