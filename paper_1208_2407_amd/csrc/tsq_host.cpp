@@ -319,7 +319,7 @@ bool pass_groups(const tsq_plan* p, int64_t steps, int S, std::vector<PassGroup>
 // Steps of pass i: the steps + 1 stages (the closing odd factors are one) dealt
 // evenly, so no pass runs more than ceil((steps + 1) / passes) stages.
 int64_t tile_steps_before(const TilePasses& t, int64_t steps, int64_t i) {
-    return i == t.passes ? steps : (int64_t)((__int128)(steps + 1) * i / t.passes);
+    return i == t.passes ? steps : (int64_t)(((__int128)steps + 1) * i / t.passes);
 }
 
 // Whether the tile kernels run this evolution, and in how many passes: the
@@ -367,7 +367,7 @@ TilePasses pick_tile(const tsq_plan* p, int64_t steps, bool td) {
             const int64_t n = (g.tiles + cus - 1) / cus;
             if (n > 2) continue;
             const double t = launch + 0.1 * mb + (double)n * (rp == 1 ? 1.3 + 0.6 * Kr : 2.0 + 1.0 * Kr);
-            int64_t passes = u4 ? steps : (steps + 1 + K - 1) / K;
+            int64_t passes = u4 ? steps : steps / K + 1;  // ceil((steps + 1) / K)
             if (!u4 && (passes & 1) && steps > 1) ++passes;  // an odd count ends with a copy
             if (!u4 && steps == 1) passes = 1;
             const double c = t * (double)passes;
