@@ -173,10 +173,11 @@ int tsq_evolve_passes(const tsq_plan* plan, int64_t steps, int64_t* passes, int3
  * eps_l = V_l + hbar^2/(m a^2) per axis) acts through exp(-i dt eps_l / hbar):
  * build that phase table exp(-i dt (V_l + eps0) / hbar) in FP64 from the device
  * array V_dev (nx*ny doubles) into the workspace `ws` of `ws_bytes` bytes
- * (device, 256-byte aligned).  On 2D meshes the table also carries the
- * cosines the tangent-form rotations leave out (see tsq_evolve).  complex128
- * stores it in FP64; complex64 as two int32 fixed-point parts scaled by 2^30
- * (8 bytes per site, about 31 bits each).
+ * (device, 256-byte aligned).  The table also carries the cosines the
+ * tangent-form rotations leave out (see tsq_evolve).  complex128 stores it in
+ * FP64; complex64 as two int32 fixed-point parts scaled by 2^30 (3D meshes: by
+ * the power of two that takes the entries' modulus to between 2^30 and 2^31),
+ * 8 bytes per site, about 31 bits each.
  * Records `ws`; tsq_evolve must be given the same workspace.
  * Errors: TSQ_ERR_ARG (null), TSQ_ERR_WORKSPACE, TSQ_ERR_DEVICE. */
 int tsq_set_potential(tsq_plan* plan, const double* V_dev, void* ws, size_t ws_bytes,

@@ -200,12 +200,13 @@ struct C64 {
 
 // Phase table entry -> phase factor.  complex128: exp(-i phi) as is.
 // complex64: the table holds cos(phi) and -sin(phi) as 32-bit fixed-point
-// numbers (scale 2^30; 8 bytes, the size of a complex64, but about 31 bits
-// per part instead of 24, so the coherent per-site error of a rounded table,
-// repeated every step, stays below 7e-10 per step); they split exactly into a
-// hi float (bits 8 and up, 23 of them with the sign apart) and a lo float (the
-// low byte, which one conversion extracts), the pair the complex64 phase
-// multiply takes.
+// numbers (scale 2^30 in 2D, `sc` its inverse; in 3D slab_table_unit; 8 bytes,
+// the size of a complex64, but about 31 bits per part instead of 24, so the
+// coherent per-site error of a rounded table, repeated every step, is 4.7e-10 per
+// part and step at modulus 1); they split exactly into a hi float (bits 8 and up,
+// 23 of them and the sign) and a lo float (the low byte, which one conversion
+// extracts), the pair the complex64 phase multiply takes: together all bits of
+// the entry, whichever bit they part at.
 __device__ __forceinline__ double2 decode_phase(double2 t, double = 1.0) { return t; }
 __device__ __forceinline__ float4 decode_phase(int2 t, float sc = 0x1p-30f) {
     return make_float4((float)(t.x & ~0xff) * sc, (float)(t.y & ~0xff) * sc,
