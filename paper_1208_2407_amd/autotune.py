@@ -149,6 +149,9 @@ def tune(plan, psi, *, candidates: Optional[Iterable[Schedule]] = None, steps: i
     for cand in (candidates or DEFAULT_CANDIDATES):
         run(cand)
     best = pick(timed)
+    # before the segment heights: a tall one leaves most of the chip idle, and what is
+    # timed right after it meets lower clocks (10% at 2048^2)
+    library = run(LIBRARY) if candidates is None and plan.problem.nz < 2 else None
     if segments and candidates is None:
         base = next(ms for ms, c in timed if c == best)
         seg_timed = [(base, best)]
@@ -161,10 +164,8 @@ def tune(plan, psi, *, candidates: Optional[Iterable[Schedule]] = None, steps: i
         fastest = min(seg_timed)
         if fastest[0] < base * (1.0 - TIE):
             best = fastest[1]
-    if candidates is None and plan.problem.nz < 2:
-        explicit = next(ms for ms, c in timed if c == best)
-        if run(LIBRARY) < explicit * (1.0 - TIE):
-            best = LIBRARY
+    if library is not None and library < next(ms for ms, c in timed if c == best) * (1.0 - TIE):
+        best = LIBRARY
     del scratch
     plan.set_schedule(*best)
     if use_cache:
