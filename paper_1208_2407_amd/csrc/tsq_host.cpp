@@ -563,13 +563,20 @@ void append_launch(tsq_batch* b, int steps, bool last, const std::vector<tsq::Pa
         d.seg_rows = (int)std::min<long long>(h, d.ny);
         const tsq::MarchGeometry g = tsq::march_geometry(d.nx, d.ny, steps, last, ppl, d.seg_rows);
         jobs.push_back(tsq::batch_job(tsq::make_march_args<R>(d, g)));
-        // neighbouring strips of a segment next to each other: a block's
-        // wavefronts read the halo columns they share at about the same time
-        for (int sg = 0; sg < g.nsegs; ++sg)
-            for (int st = 0; st < g.nstrips; ++st) {
-                const int rows = std::min(d.seg_rows, d.ny - sg * d.seg_rows);
-                tiles.push_back(tsq::BatchTile{(int)j, st, sg, rows});
-            }
+        // a block's wavefronts take consecutive tiles, so that they read the halo they
+        // share at about the same time: neighbouring strips of a segment, or, in
+        // complex128, neighbouring segments of a strip whose row pairs are fewer than their
+        // halo's on one side.  us per call, strips and segments next to each other: 48
+        // problems, 3 steps per pass, 2-row tiles 664 and 499; 3 of 64 to 512 at the
+        // library's heights, 6 steps, 75 and 69; complex64 those at 16 rows, 3 steps, 50.8
+        // and 52.2
+        const bool down = sizeof(R) == 8 && d.seg_rows / 2 < steps + (last ? 1 : 0);
+        const int inner = down ? g.nsegs : g.nstrips;
+        for (int i = 0; i < g.nsegs * g.nstrips; ++i) {
+            const int a = i / inner, c = i % inner, st = down ? a : c, sg = down ? c : a;
+            const int rows = std::min(d.seg_rows, d.ny - sg * d.seg_rows);
+            tiles.push_back(tsq::BatchTile{(int)j, st, sg, rows});
+        }
     }
     std::stable_sort(tiles.begin(), tiles.end(),
                      [](const tsq::BatchTile& x, const tsq::BatchTile& y) { return x.rows > y.rows; });
