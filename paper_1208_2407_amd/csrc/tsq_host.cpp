@@ -175,7 +175,7 @@ int seg_rows_on(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool
     const long long groups = (g.nstrips + tsq::kWavesPerBlock - 1) / tsq::kWavesPerBlock;
     // one or two strips leave most of a block's wavefronts empty: so many more blocks
     const int fold = std::max(1, tsq::kWavesPerBlock / g.nstrips);
-    const int fits = g.nstrips == 1 && !lds && !c128 ? std::max(occ, 3) : occ;
+    const int fits = g.nstrips == 1 && !lds && !c128 && occ > 1 ? std::max(occ, 3) : occ;
     const bool all = steps <= 2 && (c128 || (td && !closed && (long long)p->p.nx * p->p.ny >= 8000000));
     const int full = all ? occ : (c128 ? 1 : 2) * fold;
     const long long segs = std::max(1LL, (long long)cus * std::min(fits, full) / groups);
@@ -183,12 +183,16 @@ int seg_rows_on(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool
     if (q >= 2 * K) return (int)(2 * q);
     const double share = c128 ? 0.95 : 0.78;
     double best = 0.0;
-    for (long long t = 1; t <= 2 * K; ++t) {
+    // two pairs per lane in complex64 (16-byte stores 32 bytes apart) lose more by the
+    // halo of many segments of one pair than by longer segments, unless most units are idle:
+    // 40 x 542, 1 step, 120 with 2 rows, 95 with 4; 64^2, 2 steps, 71 and 73
+    const long long least = ppl == 2 && !c128 && 4 * groups * pairs > cus ? 2 : 1;
+    for (long long t = least; t <= 2 * K; ++t) {
         const long long blocks = groups * ((pairs + t - 1) / t);
         const long long per_simd = (blocks + (long long)cus * fold - 1) / ((long long)cus * fold);
         const long long rounds = fold == 1 ? 1 : (blocks + (long long)cus * occ - 1) / ((long long)cus * occ);
         const double cost = (double)(t + K) * std::max((double)rounds, share * (double)per_simd);
-        if (t == 1 || cost < best) {
+        if (t == least || cost < best) {
             best = cost;
             q = t;
         }
