@@ -151,9 +151,10 @@ int occupancy_cached(int dtype, int steps, bool last, int ppl, bool lds, bool cl
 // us with two blocks a unit, 69.8 with four; 2048^2 complex128 fourth order 54
 // with one, 67 with two).  complex128 passes of one or two steps take all the
 // blocks that fit: their loads are far apart (1000 x 6218, 2 steps: 118 against 136
-// with one a unit; 2048^2 85 against 76), and so do large driven complex64 meshes (16
-// bytes of table a site; 4 passes of 4096^2 399 against 431, 8 steps of 3168 x 4834 371
-// against 382, but 2000^2 1.07 to 1.14 times faster with two).  A mesh of one or two strips fills a
+// with one a unit; 2048^2 85 against 76), and so do driven complex64 meshes of 14M sites
+// and more (16 bytes of table a site; 8 steps in 4 passes, all blocks against two a unit:
+// 4000^2 402 and 425, 4200^2 451 and 468, 8000^2 1700 and 1721; below, 12 steps in 6
+// passes: 3600^2 471 and 436, 3000^2 331 and 289).  A mesh of one or two strips fills a
 // quarter or half of a block: as many more blocks count as one (42 x 6218, complex64,
 // 2 steps, 11.4 against 14.4), and three of one strip fit a unit in complex64 where
 // two full ones do (100 x 60000, 20 steps: 224 with three, 311 with two; complex128,
@@ -176,7 +177,7 @@ int seg_rows_on(const tsq_plan* p, int steps, bool last, int ppl, bool lds, bool
     // one or two strips leave most of a block's wavefronts empty: so many more blocks
     const int fold = std::max(1, tsq::kWavesPerBlock / g.nstrips);
     const int fits = g.nstrips == 1 && !lds && !c128 && occ > 1 ? std::max(occ, 3) : occ;
-    const bool all = steps <= 2 && (c128 || (td && !closed && (long long)p->p.nx * p->p.ny >= 8000000));
+    const bool all = steps <= 2 && (c128 || (td && !closed && (long long)p->p.nx * p->p.ny >= 14000000));
     const int full = all ? occ : (c128 ? 1 : 2) * fold;
     const long long segs = std::max(1LL, (long long)cus * std::min(fits, full) / groups);
     long long q = (pairs + segs - 1) / segs;
